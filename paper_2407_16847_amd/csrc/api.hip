@@ -106,6 +106,15 @@ splat_status upload(splat_acsr* h) {
   h->dev.nnz = a.nnz;
   h->dev.max_row_nnz = a.max_row_nnz;
   h->dev.n_groups = (int32_t)a.groups.size();
+  h->dev.computed = a.computed;
+  h->dev.max_slice_tiles = 0;
+  for (const splat::Group& g : a.groups)
+    for (int w = 0; w < splat::kWavesPerGroup; ++w) {
+      int32_t n = 0;
+      for (int32_t t = g.tile_begin; t < g.tile_end; ++t)
+        n += ((a.tiles[t].flags >> (splat::kWaveShift + 2 * w)) & 3) != splat::kWaveEmpty;
+      h->dev.max_slice_tiles = std::max(h->dev.max_slice_tiles, n);
+    }
   h->dev.row_ptr = (const int32_t*)dst[0];
   h->dev.runs = (const splat::RowRuns*)dst[1];
   h->dev.rows = (const int32_t*)dst[2];
@@ -543,7 +552,7 @@ splat_status splat_sparse_mhsa_fwd(splat_acsr_t h, splat_dtype dtype, int32_t B,
   if (dtype == SPLAT_BF16)
     return launched(splat::launch_fused_mfma(h->dev, B * H, d, Q, K, V, scale, O, out_dtype, st),
                     "sparse_mhsa_fwd");
-  return launched(splat::launch_fused_rows(h->dev, dtype, B * H, d, Q, K, V, scale, O, out_dtype, st),
+  return launched(splat::launch_fused_f32(h->dev, B * H, d, Q, K, V, scale, O, out_dtype, st),
                   "sparse_mhsa_fwd");
 }
 
@@ -609,6 +618,7 @@ splat_status splat_debug_bounds(uint32_t* flags, int32_t clear) {
   if (e == hipSuccess) e = splat::bounds_collect_rows(&bits, clear != 0);
   if (e == hipSuccess) e = splat::bounds_collect_mfma(&bits, clear != 0);
   if (e == hipSuccess) e = splat::bounds_collect_tiles(&bits, clear != 0);
+  if (e == hipSuccess) e = splat::bounds_collect_slices(&bits, clear != 0);
   if (e != hipSuccess) return fail(SPLAT_ERR_HIP, "splat_debug_bounds: %s", hipGetErrorString(e));
   *flags = bits;
   return SPLAT_OK;

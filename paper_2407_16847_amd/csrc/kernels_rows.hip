@@ -4,7 +4,7 @@
 // 5.1: the k-th value of run r sits at column start + stride * k) and serve
 // every dtype and pattern: they are the fp32 path (fp32 FMA throughout, the
 // library's accurate path) and run any request the matrix-core kernels do
-// not take.  Lanes own keys (SDDMM, fused) or output features (SpMM).
+// not take.  Lanes own keys (SDDMM) or output features (SpMM).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -20,28 +20,6 @@ __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ void store(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store(__bf16* p, float v) { *p = (__bf16)v; }
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-// column of the k-th value of a row (k < row nnz)
-__device__ __forceinline__ int col_of(const RowRuns& rr, int k) {
-  int j = 0;
-#pragma unroll
-  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
-    const Run q = rr.r[r];
-    if (k >= q.prefix && k < q.prefix + q.count) j = q.start + q.stride * (k - q.prefix);
-  }
-  return j;
-}
 
 // dot(qs[0:d], row[0:d]) in fp32, sequential FMA over the features
 template <typename T>
@@ -110,58 +88,6 @@ __global__ __launch_bounds__(kWave) void k_rspmm_rows(DevAcsr a, int d, const fl
   if (two) store(o + lane + kWave, acc1);
 }
 
-// Online softmax (running max m, running sum l) over the row's keys, 64 keys
-// per step; fp32 throughout.
-template <typename T, typename OutT>
-__global__ __launch_bounds__(kWave) void k_fused_rows(DevAcsr a, int d, const T* __restrict__ Q,
-                                                      const T* __restrict__ K,
-                                                      const T* __restrict__ V, float scale,
-                                                      OutT* __restrict__ O) {
-  const int i = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
-  __shared__ float qs[128];
-  __shared__ float ps[kWave];
-  __shared__ int js[kWave];
-  const size_t head = (size_t)bh * a.L * d;
-  for (int c = lane; c < d; c += kWave) qs[c] = to_f32(Q[head + (size_t)i * d + c]);
-  __syncthreads();
-  const RowRuns rr = a.runs[i];
-  const int n = a.row_ptr[i + 1] - a.row_ptr[i];
-  const bool two = d > kWave;
-  float m = -INFINITY, l = 0.f, acc0 = 0.f, acc1 = 0.f;
-  for (int k0 = 0; k0 < n; k0 += kWave) {
-    const int k = k0 + lane;
-    const bool valid = k < n;
-    int j = 0;
-    float s = -INFINITY;
-    if (valid) {
-      j = dbg::idx(col_of(rr, k), a.L, dbg::kKey);
-      s = dot_row(qs, K + head + (size_t)j * d, d) * scale;
-    }
-    const float mn = fmaxf(m, wave_max(s));      // finite: lane 0 is valid
-    const float alpha = expf(m - mn);            // 0 on the first step (m = -inf)
-    const float p = valid ? expf(s - mn) : 0.f;
-    l = l * alpha + wave_sum(p);
-    acc0 *= alpha;
-    acc1 *= alpha;
-    ps[lane] = p;
-    js[lane] = j;
-    __syncthreads();
-    const int cnt = min(kWave, n - k0);
-    for (int t = 0; t < cnt; ++t) {
-      const float pt = ps[t];
-      const T* v = V + head + (size_t)js[t] * d;
-      acc0 = fmaf(pt, to_f32(v[lane]), acc0);
-      if (two) acc1 = fmaf(pt, to_f32(v[lane + kWave]), acc1);
-    }
-    __syncthreads();
-    m = mn;
-  }
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  OutT* o = O + head + (size_t)i * d;
-  store(o + lane, acc0 * inv);
-  if (two) store(o + lane + kWave, acc1 * inv);
-}
-
 #ifdef SPLAT_DEBUG_BOUNDS
 // One index check on the device (the checked build's own test): out = the
 // checked index.
@@ -225,26 +151,6 @@ hipError_t launch_rspmm_rows(const DevAcsr& a, int dtype, int BH, int d, const f
                       : rspmm_t<__bf16, true>(a, BH, d, P, V, O, out_dtype, st);
   return dtype == 0 ? rspmm_t<float, false>(a, BH, d, P, V, O, out_dtype, st)
                     : rspmm_t<__bf16, false>(a, BH, d, P, V, O, out_dtype, st);
-}
-
-template <typename T>
-static hipError_t fused_t(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
-                          const void* V, float scale, void* O, int out_dtype, hipStream_t st) {
-  dim3 grid(a.L, BH);
-  if (out_dtype == 0)
-    hipLaunchKernelGGL((k_fused_rows<T, float>), grid, dim3(kWave), 0, st, a, d, (const T*)Q,
-                       (const T*)K, (const T*)V, scale, (float*)O);
-  else
-    hipLaunchKernelGGL((k_fused_rows<T, __bf16>), grid, dim3(kWave), 0, st, a, d, (const T*)Q,
-                       (const T*)K, (const T*)V, scale, (__bf16*)O);
-  return hipGetLastError();
-}
-
-hipError_t launch_fused_rows(const DevAcsr& a, int dtype, int BH, int d, const void* Q,
-                             const void* K, const void* V, float scale, void* O, int out_dtype,
-                             hipStream_t st) {
-  return dtype == 0 ? fused_t<float>(a, BH, d, Q, K, V, scale, O, out_dtype, st)
-                    : fused_t<__bf16>(a, BH, d, Q, K, V, scale, O, out_dtype, st);
 }
 
 }  // namespace splat

@@ -1,0 +1,629 @@
+// kernels_slices.hip -- matrix-core kernels whose workgroup owns 32 query rows
+// (a slice: one wavefront's rows of a row group) of one head, its four
+// wavefronts sharing out the slice's keys.
+//
+// A wavefront's unit of work is half a key tile: 32 keys.  Of the slice's
+// non-empty tiles (in order), wavefront w takes the tiles of parity w / 2 and,
+// of each, half w % 2.  Nothing is shared while the units are walked, so there
+// is no barrier: a unit's K rows come through the wavefront's own LDS, one
+// unit ahead, its V rows straight into the operand registers.  At the end the
+// four partial results are combined through LDS.
+//
+// Operands (lane = 32 h + i): S^T = K Q^T with lane i holding key i's (A) or
+// query i's (B) features in chunks of 16 bytes, halves h alternating -- any
+// order of the features will do as long as both sides use the same -- and
+// the scores of ONE query, keys 8 (r/4) + 4 h + r % 4, in registers r = 0..15.
+// O^T += V^T P^T takes P^T straight from those registers; lane i reads
+// features NB i .. NB i + NB - 1 (NB = d / 32) of the key rows the registers
+// imply, whole rows per load, so output row i of block b is feature NB i + b.
+#include <hip/hip_runtime.h>
+#include <math.h>
+
+#include <type_traits>
+
+#include "bounds.hpp"
+#include "launch.hpp"
+#include "mfma_util.hpp"
+
+namespace splat {
+namespace {
+
+using namespace mfma;
+
+constexpr int kThreads = 256;            // 4 wavefronts, one slice
+constexpr int kUnit = 32;                // keys per unit
+constexpr int kMaxGridY = 32768;         // slices per launch dimension; more are looped over
+constexpr float kRefSlack = 8.f;
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+// ---------------------------------------------------------------- operands
+template <typename T, int D>
+struct Mat;
+
+// fp32: v_mfma_f32_32x32x2_f32 (fp32 products, fp32 sums)
+template <int D>
+struct Mat<float, D> {
+  static constexpr int NB = D / 32;
+  typedef typename std::conditional<NB == 2, f32x2_t, f32x4_t>::type vrow_t;
+  struct Row {               // features 8 t + 4 h .. + 3 of a Q or K row
+    f32x4_t v[D / 8];
+  };
+  struct V {                 // features NB i .. of 8 key rows: half j of a unit
+    vrow_t v[8];
+  };
+  static __device__ __forceinline__ f32x16_t dot(const Row& k, const Row& q) {
+    f32x16_t s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int t = 0; t < D / 8; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(k.v[t][e], q.v[t][e], s, 0, 0, 0);
+    return s;
+  }
+  static __device__ __forceinline__ void pv(f32x16_t (&o)[NB], const V& v, const float (&p)[16],
+                                            int j) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.v[r][b], p[8 * j + r], o[b], 0, 0, 0);
+  }
+};
+
+// K or Q row: 16-byte chunks 2 t + h, t < D * sizeof(T) / 32
+template <typename T, int D>
+__device__ __forceinline__ void load_row(typename Mat<T, D>::Row& x, const char* base,
+                                         unsigned off) {
+  constexpr int N = D * (int)sizeof(T) / 32;
+#pragma unroll
+  for (int t = 0; t < N; ++t)
+    x.v[t] = *(const typename std::remove_reference<decltype(x.v[0])>::type*)(base + off + 32 * t);
+}
+
+// ------------------------------------------------------------ units of work
+struct Unit {
+  int kb, ks, n;       // keys kb + ks * u, u < n (n <= 32)
+  int mask_block;
+  int half;            // which half of the tile
+  bool full;           // every key in every row of the slice
+};
+
+// Walks the slice's non-empty tiles and yields this wavefront's units.  The
+// 64 lanes hold 64 tile descriptors at a time, so a unit costs no dependent
+// load.
+struct Units {
+  const Tile* tiles;   // the group's first tile
+  int nt, base, rank, lane, wave, slice;
+  uint64_t left;       // non-empty tiles of the current 64 not yet visited
+  int4 d;
+  int mb;
+
+  __device__ __forceinline__ void fetch() {
+    d = make_int4(0, 1, 0, 0);
+    mb = -1;
+    if (base + lane < nt) {
+      const Tile* t = tiles + base + lane;
+      d = *(const int4*)t;
+      mb = t->mask_block;
+    }
+    left = __ballot(((d.w >> (kWaveShift + 2 * slice)) & 3) != kWaveEmpty);
+  }
+  __device__ __forceinline__ void start(const Tile* t, int n, int lane_, int wave_, int slice_) {
+    tiles = t, nt = n, base = 0, rank = 0, lane = lane_, wave = wave_, slice = slice_;
+    fetch();
+  }
+  __device__ __forceinline__ bool next(Unit& u) {
+    const int half = wave & 1;
+    while (true) {
+      while (left == 0) {
+        base += 64;
+        if (base >= nt) return false;
+        fetch();
+      }
+      const int t = __builtin_ctzll(left);
+      left &= left - 1;
+      const bool mine = (rank & 1) == (wave >> 1);
+      ++rank;
+      const int nk = __builtin_amdgcn_readlane(d.z, t) - kUnit * half;
+      if (!mine || nk <= 0) continue;
+      u.ks = __builtin_amdgcn_readlane(d.y, t);
+      u.kb = __builtin_amdgcn_readlane(d.x, t) + u.ks * kUnit * half;
+      u.n = min(nk, kUnit);
+      u.mask_block = __builtin_amdgcn_readlane(mb, t);
+      u.half = half;
+      const int st = (__builtin_amdgcn_readlane(d.w, t) >> (kWaveShift + 2 * slice)) & 3;
+      u.full = st == kWaveFull;
+      return true;
+    }
+  }
+};
+
+// A wavefront's view of its slice.
+struct Slice {
+  int lane, wave, qi, h, w;    // w: the slice's place in its group
+  int row, tb, nt;
+  bool row_valid;
+  const uint32_t* masks;       // the slice's 32-bit mask words, two per row
+
+  // false: the slice has no row
+  __device__ __forceinline__ bool open(int s, const Group* groups, const int32_t* rows,
+                                       const uint64_t* m, int L) {
+    const Group grp = groups[s / kWavesPerGroup];
+    w = s % kWavesPerGroup;
+    if (w * kWaveRows >= grp.nrows) return false;
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    qi = lane & 31, h = lane >> 5;
+    const int i = w * kWaveRows + qi;
+    row_valid = i < grp.nrows;
+    row = row_valid ? dbg::idx(rows[grp.row_off + i], L, dbg::kRow) : 0;
+    tb = grp.tile_begin, nt = grp.tile_end - grp.tile_begin;
+    masks = (const uint32_t*)m + 2 * i;
+    return true;
+  }
+  // the row's membership bits in a unit
+  __device__ __forceinline__ uint32_t bits(const Unit& u) const {
+    return u.full ? ~0u : masks[(size_t)u.mask_block * (2 * kBM) + u.half];
+  }
+  __device__ __forceinline__ int key(const Unit& u, int k, int L) const {
+    return dbg::idx(u.kb + u.ks * min(k, u.n - 1), L, dbg::kKey);
+  }
+};
+
+// A unit's K rows go from memory into the wavefront's own LDS, 1 KB of whole
+// rows per load, and from there into the operand: loaded straight into the
+// operand, each load would touch 32 rows, 32 bytes of each, and K would hold
+// registers a unit ahead (d = 128: 862 us against 631, full mask, L = 2048,
+// 32 heads).  The 16-byte chunks of row r sit XOR-ed with r % 16, so that the
+// operand reads (16 lanes, 16 rows) are free of bank conflicts.  Keys past the
+// unit's end re-read its last.
+template <typename T, int D>
+__device__ __forceinline__ void fetch_k(float* stage, const char* Kh, const Slice& s, const Unit& u,
+                                        int L) {
+  constexpr int RB = D * (int)sizeof(T), CPR = RB / 16, RPL = 64 / CPR;
+#pragma unroll
+  for (int k = 0; k < kUnit / RPL; ++k) {
+    const int r = RPL * k + s.lane / CPR;
+    const int c = (s.lane % CPR) ^ (r & 15);
+    dma16(Kh + ((unsigned)s.key(u, r, L) * (unsigned)RB + 16u * c), (char*)stage + kDmaBlock * k);
+  }
+}
+template <typename T, int D>
+__device__ __forceinline__ void load_k(typename Mat<T, D>::Row& x, const float* stage,
+                                       const Slice& s) {
+  constexpr int RB = D * (int)sizeof(T);
+  const int off = s.qi * RB + 16 * (s.h ^ (s.qi & 15));
+#pragma unroll
+  for (int t = 0; t < RB / 32; ++t)
+    x.v[t] = *(const typename std::remove_reference<decltype(x.v[0])>::type*)((const char*)stage +
+                                                                             (off ^ (32 * t)));
+}
+// waits for this wavefront's LDS reads, and for its loads from memory
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void load_v(typename Mat<T, D>::V& x, const char* Vh, const Slice& s,
+                                       const Unit& u, int j, int L) {
+  using vrow_t = typename Mat<T, D>::vrow_t;
+  constexpr unsigned RB = D * sizeof(T);
+  if (u.n == kUnit) {
+    // whole unit: one lane offset, the rows' offsets are uniform
+    const unsigned lo = (unsigned)(u.ks * 4 * s.h) * RB + (unsigned)sizeof(vrow_t) * s.qi;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int k = 16 * j + 8 * (r >> 2) + (r & 3);
+      const char* p = Vh + (size_t)((unsigned)dbg::idx(u.kb + u.ks * k, L, dbg::kKey) * RB);
+      x.v[r] = *(const vrow_t*)(p + lo);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int k = s.key(u, 16 * j + 8 * (r >> 2) + 4 * s.h + (r & 3), L);
+      x.v[r] = *(const vrow_t*)(Vh + ((unsigned)k * RB + (unsigned)sizeof(vrow_t) * s.qi));
+    }
+  }
+}
+
+// scores outside the row's runs set to -inf
+__device__ __forceinline__ void mask_unit(float (&t)[16], uint32_t bits, int h) {
+  const unsigned word = bits >> (4 * h);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) t[r] = keep_if_bit(t[r], word, 8 * (r >> 2) + (r & 3));
+}
+
+// The matrix cores multiply every key row by every query's weight, 0 for the
+// queries that do not have the key, and 0 * inf is NaN.  z turns NaN when V
+// holds an infinity or a NaN in half a unit in which some row lacks some key;
+// the slice is then redone row by row (the *_row functions below).  With bf16
+// V no such check is made: there a row may see the keys of its tile.
+template <typename T, int D>
+__device__ __forceinline__ void check_v(float& z, const typename Mat<T, D>::V& v, const Unit& u) {
+  if constexpr (std::is_same<T, float>::value) {
+    if (!u.full) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b) z = fmaf(v.v[r][b], 0.f, z);
+    }
+  }
+}
+
+// --------------------------------------------------------- combining, output
+// LDS of a slice kernel: each wavefront's partial O (its staging area before
+// that), the row references and sums.
+template <int D>
+struct Shared {
+  static constexpr int OS = D + 4;                 // floats per staged O row
+  float o[kWavesPerGroup][kWaveRows * OS];
+  float m[kWavesPerGroup][kWaveRows];
+  float l[kWavesPerGroup][kWaveRows];
+  int redo;                                        // some V value is not finite
+};
+
+template <typename OutT>
+__device__ __forceinline__ void store_o4(OutT* p, f32x4_t v) {
+  store4<OutT>(p, v[0], v[1], v[2], v[3]);
+}
+
+// Sum of the wavefronts' O^T, times inv(row i), written as whole rows: every
+// thread sums four features of one row at a time, eight lanes along a row.
+template <int D, typename OutT, typename F>
+__device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 32], const Slice& s,
+                                        OutT* Oh, F&& inv) {
+  constexpr int NB = D / 32, OS = Shared<D>::OS;
+  float* const mine = sh.o[s.wave] + s.qi * OS;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {      // features NB (8 g + 4 h) + 4 c .. + 3
+      f32x4_t v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = o[(4 * c + e) % NB][4 * g + (4 * c + e) / NB];
+      *(f32x4_t*)(mine + NB * (8 * g + 4 * s.h) + 4 * c) = v;
+    }
+  __syncthreads();
+  const int r = threadIdx.x >> 3;                  // row of the slice
+  const int lane_r = (int)__shfl(s.row_valid ? s.row : -1, r & 31, 64);
+  if (lane_r >= 0) {
+    const float f = inv(r, lane_r);
+    OutT* const orow = Oh + (size_t)lane_r * D;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int c = 4 * (threadIdx.x & 7) + 32 * k;
+      f32x4_t v = *(const f32x4_t*)(sh.o[0] + r * OS + c);
+#pragma unroll
+      for (int w = 1; w < kWavesPerGroup; ++w) v += *(const f32x4_t*)(sh.o[w] + r * OS + c);
+      store_o4<OutT>(orow + c, v * f);
+    }
+  }
+}
+
+// ---------------------------------------------------------- one row, VALU
+// column of the k-th value of a row (k < row nnz)
+__device__ __forceinline__ int col_of(const RowRuns& rr, int k) {
+  int j = 0;
+#pragma unroll
+  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
+    const Run q = rr.r[r];
+    if (k >= q.prefix && k < q.prefix + q.count) j = q.start + q.stride * (k - q.prefix);
+  }
+  return j;
+}
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+__device__ __forceinline__ void store1(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store1(__bf16* p, float v) { *p = (__bf16)v; }
+
+// The fused forward of row i by one wavefront: scores by lanes over 64 keys at
+// a time, O by lanes over the features; only the row's own keys are read.
+template <int D, typename OutT>
+__device__ __forceinline__ void fused_row(int i, int lane, const RowRuns* runs,
+                                          const int32_t* row_ptr, int L, const float* Qh,
+                                          const float* Kh, const float* Vh, float scale,
+                                          OutT* Oh) {
+  constexpr int NC = D / 64;
+  const RowRuns rr = runs[i];
+  const int n = row_ptr[i + 1] - row_ptr[i];
+  const float* const q = Qh + (size_t)i * D;
+  float m = -INFINITY, l = 0.f, acc[NC];
+#pragma unroll
+  for (int b = 0; b < NC; ++b) acc[b] = 0.f;
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += 64) {
+    const bool valid = k0 + lane < n;
+    int j = 0;
+    float x = -INFINITY;
+    if (valid) {
+      j = dbg::idx(col_of(rr, k0 + lane), L, dbg::kKey);
+      const float* const k = Kh + (size_t)j * D;
+      float d[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < D; c += 4) {
+        const f32x4_t kv = *(const f32x4_t*)(k + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = fmaf(q[c + e], kv[e], d[e]);
+      }
+      x = ((d[0] + d[1]) + (d[2] + d[3])) * scale;
+    }
+    const float mn = fmaxf(m, wave_max(x));
+    const float alpha = expf(m - mn);            // 0 on the first step (m = -inf)
+    const float p = valid ? expf(x - mn) : 0.f;
+    l = l * alpha + wave_sum(p);
+#pragma unroll
+    for (int b = 0; b < NC; ++b) acc[b] *= alpha;
+    auto key = [&](int t) {
+      const float pt = __builtin_bit_cast(
+          float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p), t));
+      const float* const v = Vh + (size_t)__builtin_amdgcn_readlane(j, t) * D;
+#pragma unroll
+      for (int b = 0; b < NC; ++b) acc[b] = fmaf(pt, v[64 * b + lane], acc[b]);
+    };
+    const int cnt = min(64, n - k0);
+    int t = 0;
+#pragma unroll 1
+    for (; t + 8 <= cnt; t += 8)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) key(t + e);
+#pragma unroll 1
+    for (; t < cnt; ++t) key(t);
+    m = mn;
+  }
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+  for (int b = 0; b < NC; ++b) store1(Oh + (size_t)i * D + 64 * b + lane, acc[b] * inv);
+}
+
+// One wavefront per row: the launches too small for the slices below.
+template <int D, typename OutT>
+__global__ __launch_bounds__(kThreads) void k_fused_rows(
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs, int L,
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    float scale, OutT* __restrict__ O) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = blockIdx.y * 4 + wave;
+  if (i >= L) return;
+  const size_t head = (size_t)blockIdx.x * L * D;
+  fused_row<D, OutT>(i, threadIdx.x & 63, runs, row_ptr, L, Q + head, K + head, V + head, scale,
+                     O + head);
+}
+
+// ------------------------------------------------------------- fused forward
+// O = softmax_nz(scale * M (x) Q K^T) V, the online softmax per wavefront over
+// its units, the four (reference, sum, O) combined at the end.  A row takes its
+// first unit's maximum as its reference and keeps it while later maxima stay
+// within 2^kRefSlack of it: p then lies in [0, 2^kRefSlack], in fp32 as exact
+// as below 1, and few units rescale O.
+//
+// fp32 is bound by the matrix cores: a unit is 64 (d = 64) v_mfma_f32_32x32x2
+// of 64 cycles.  Full mask, L = 2048, 64 heads, d = 64: 651 us, 106 TFLOP/s of
+// the 153 that a large fp32 matrix product reaches (without the loads of K and
+// V 127); a wavefront per row (lanes' own dot products) ran at 7 TFLOP/s.
+// Window 256 + 32 global, L = 2048, 12 heads: 620 -> 59 us; there the slice of
+// the global rows, 16 units per wavefront, is the longest chain.  Two
+// wavefronts per SIMD; three (168 registers, some spilled) took 86 us against
+// 63, and the next unit's products beside this one's softmax 65 against 60.
+template <typename T, int D, typename OutT>
+__global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
+    const Group* __restrict__ groups, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
+    const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks, int L, int n_slices,
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, float scale,
+    OutT* __restrict__ O) {
+  using M = Mat<T, D>;
+  constexpr int NB = D / 32;
+  __shared__ __attribute__((aligned(16))) Shared<D> sh;
+  const size_t head = (size_t)blockIdx.x * L * D;
+  const char* Kh = (const char*)(K + head);
+  const char* Vh = (const char*)(V + head);
+  // sl2 = scale * log2(e) > 0: the sign of a negative scale, and a zero one, go to Q
+  const float sl2 = scale == 0.f ? 1.f : fabsf(scale) * 1.4426950408889634f;
+  const float sgn = scale == 0.f ? 0.f : copysignf(1.f, scale);
+  for (int sl = blockIdx.y; sl < n_slices; sl += gridDim.y) {
+    Slice s;
+    if (!s.open(sl, groups, rows, masks, L)) continue;
+    typename M::Row q;
+    load_row<T, D>(q, (const char*)(Q + head),
+                   (unsigned)s.row * (D * (unsigned)sizeof(T)) + 16u * s.h);
+    for (auto& x : q.v) x *= sgn;
+    f32x16_t o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    // the row's reference (log2 domain) and the sum of this half's keys
+    float m = -INFINITY, l = 0.f;
+    float z = 0.f;
+    if (threadIdx.x == 0) sh.redo = 0;
+
+    float* const stage = sh.o[s.wave];
+    Units it;
+    it.start(tiles + s.tb, s.nt, s.lane, s.wave, s.w);
+    Unit u;
+    bool more = it.next(u);
+    if (more) fetch_k<T, D>(stage, Kh, s, u, L);
+    while (more) {
+      // d = 128: V is loaded where no K is held, half a unit at a time, which
+      // keeps the kernel in 256 registers (two wavefronts per SIMD)
+      wait_loads();
+      typename M::Row k;
+      load_k<T, D>(k, stage, s);
+      typename M::V v0, v1;
+      if (D == 64) load_v<T, D>(v0, Vh, s, u, 0, L);
+      const uint32_t bits = s.bits(u);
+      const f32x16_t acc = M::dot(k, q);
+      if (D != 64) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_v<T, D>(v0, Vh, s, u, 0, L);
+      }
+      Unit nu;
+      const bool next = it.next(nu);
+      if (next) fetch_k<T, D>(stage, Kh, s, nu, L);
+      float p[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[r] = acc[r];
+      if (!u.full) mask_unit(p, bits, s.h);
+      float mx0 = p[0], mx1 = p[8];
+#pragma unroll
+      for (int r = 1; r < 8; ++r) {
+        mx0 = fmaxf(mx0, p[r]);
+        mx1 = fmaxf(mx1, p[8 + r]);
+      }
+      float mx = fmaxf(mx0, mx1);
+      mx = fmaxf(mx, lane_xor32(mx)) * sl2;
+      if (__any(mx > m + kRefSlack)) {
+        const float mn = mx > m + kRefSlack ? mx : m;
+        const float alpha = m == -INFINITY ? 0.f : exp2_hw(m - mn);
+        l *= alpha;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
+        m = mn;
+      }
+      const float mu = m == -INFINITY ? 0.f : m;   // no key yet: exp2(-inf - 0) = 0
+      float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        p[r] = exp2_hw(fmaf(p[r], sl2, -mu)), p[r + 1] = exp2_hw(fmaf(p[r + 1], sl2, -mu));
+        l0 += p[r], l1 += p[r + 1];
+      }
+      l += l0 + l1;
+      if (D == 64) load_v<T, D>(v1, Vh, s, u, 1, L);
+      check_v<T, D>(z, v0, u);
+      M::pv(o, v0, p, 0);
+      if (D != 64) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_v<T, D>(v1, Vh, s, u, 1, L);
+      }
+      check_v<T, D>(z, v1, u);
+      M::pv(o, v1, p, 1);
+      u = nu, more = next;
+    }
+
+    l += lane_xor32(l);
+    __syncthreads();
+    if (s.h == 0) sh.m[s.wave][s.qi] = m, sh.l[s.wave][s.qi] = l;
+    if constexpr (std::is_same<T, float>::value) {
+      if (z != z) sh.redo = 1;
+      __syncthreads();
+      if (sh.redo) {
+        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
+          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
+          if (i >= 0)
+            fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
+                               O + head);
+        }
+        __syncthreads();
+        continue;
+      }
+    } else {
+      __syncthreads();
+    }
+    // row i's reference over the wavefronts, and a wavefront's factor to it
+    auto top = [&](int i) {
+      return fmaxf(fmaxf(sh.m[0][i], sh.m[1][i]), fmaxf(sh.m[2][i], sh.m[3][i]));
+    };
+    auto factor = [&](float mw, float mt) { return mw == -INFINITY ? 0.f : exp2_hw(mw - mt); };
+    const float f = factor(m, top(s.qi));
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[b][r] *= f;
+    combine<D, OutT>(sh, o, s, O + head, [&](int i, int row) {
+      const float mt = top(i);
+      float lt = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWavesPerGroup; ++w) lt += sh.l[w][i] * factor(sh.m[w][i], mt);
+      if (lt > 0.f) return 1.f / lt;
+      // no key: 0; a NaN is in O already; keys that all score -inf: NaN
+      return lt == 0.f && row_ptr[row] != row_ptr[row + 1] ? NAN : 0.f;
+    });
+    __syncthreads();   // LDS is reused by the next slice
+  }
+}
+
+
+// --------------------------------------------------------------- launches
+// Grid: x over batch*head, so that with B*H a multiple of 8 a head's
+// workgroups share one XCD's L2; y over slices, heaviest groups first.
+inline int slices(const DevAcsr& a) { return a.n_groups * kWavesPerGroup; }
+inline dim3 slice_grid(const DevAcsr& a, int BH) {
+  const int n = slices(a);
+  return dim3((unsigned)BH, (unsigned)(n < kMaxGridY ? n : kMaxGridY));
+}
+
+// Whether a launch is better off with a wavefront per row.  Times in us beyond
+// a launch's own 3.2, fitted to 39 launches (4 k to 6.2 M non-zeros over all
+// heads, every mask family, d = 64 and 128), which they meet within 35%:
+//   rows:   0.65 ns a row and 0.035 ns a non-zero (d = 64) at throughput; the
+//           longest row's keys one after the other, 52 ns each
+//   slices: 16 ns a slice and 2.5 ps a computed score at throughput; the
+//           longest slice's chain, 2.6 us per two tiles.
+// Measured, rows against slices: window 16, L = 256, one head 4.9 / 7.3;
+// strided+local 8 / 64, L = 512, one head 4.5 / 10.0; window 16, L = 1024, 4
+// heads 9.1 / 7.4; blocked 64, L = 512, 4 heads 15.1 / 7.2.
+bool rows_faster(const DevAcsr& a, int BH, int d) {
+  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
+  const double rows = fmax(0.65e-3 * R + 0.035e-3 * w * E, 0.052 * w * a.max_row_nnz);
+  const double slc =
+      fmax(16e-3 * kWavesPerGroup * a.n_groups * BH + 2.5e-6 * w * (double)a.computed * BH,
+           w * (1.6 + 2.6 * ((a.max_slice_tiles + 1) / 2)));
+  return rows < slc;
+}
+
+template <int D, typename OutT>
+hipError_t fused_rows(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
+                      float scale, void* O, hipStream_t st) {
+  hipLaunchKernelGGL((k_fused_rows<D, OutT>), dim3((unsigned)BH, (unsigned)((a.L + 3) / 4)),
+                     dim3(kThreads), 0, st, a.row_ptr, a.runs, a.L, (const float*)Q,
+                     (const float*)K, (const float*)V, scale, (OutT*)O);
+  return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
+                   float scale, void* O, int out_dtype, hipStream_t st) {
+  if (rows_faster(a, BH, D))
+    return out_dtype == 0 ? fused_rows<D, float>(a, BH, Q, K, V, scale, O, st)
+                          : fused_rows<D, __bf16>(a, BH, Q, K, V, scale, O, st);
+  if (out_dtype == 0)
+    hipLaunchKernelGGL((k_fused_slices<T, D, float>), slice_grid(a, BH), dim3(kThreads), 0, st,
+                       a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, slices(a),
+                       (const T*)Q, (const T*)K, (const T*)V, scale, (float*)O);
+  else
+    hipLaunchKernelGGL((k_fused_slices<T, D, __bf16>), slice_grid(a, BH), dim3(kThreads), 0, st,
+                       a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, slices(a),
+                       (const T*)Q, (const T*)K, (const T*)V, scale, (__bf16*)O);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t bounds_collect_slices(uint32_t* bits, bool clear) { return dbg::collect(bits, clear); }
+
+hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
+                            const void* V, float scale, void* O, int out_dtype, hipStream_t st) {
+  return d == 64 ? fused_d<float, 64>(a, BH, Q, K, V, scale, O, out_dtype, st)
+                 : fused_d<float, 128>(a, BH, Q, K, V, scale, O, out_dtype, st);
+}
+
+}  // namespace splat

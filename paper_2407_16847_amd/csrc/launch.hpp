@@ -14,6 +14,8 @@ struct DevAcsr {
   int64_t nnz;
   int32_t max_row_nnz;
   int32_t n_groups;
+  int64_t computed;         // rows x keys of the non-empty wavefront tiles
+  int32_t max_slice_tiles;  // non-empty tiles of the 32 rows that have the most
   const int32_t* row_ptr;   // L + 1
   const RowRuns* runs;      // L
   const int32_t* rows;      // L (grouped)
@@ -40,9 +42,10 @@ hipError_t launch_rsddmm_rows(const DevAcsr& a, int dtype, int BH, int d, const 
 // colmajor: P holds the column-major values (requires a.cols).
 hipError_t launch_rspmm_rows(const DevAcsr& a, int dtype, int BH, int d, const float* P,
                              const void* V, void* O, int out_dtype, bool colmajor, hipStream_t st);
-hipError_t launch_fused_rows(const DevAcsr& a, int dtype, int BH, int d, const void* Q,
-                             const void* K, const void* V, float scale, void* O, int out_dtype,
-                             hipStream_t st);
+
+// fp32: on the matrix cores, a workgroup per 32 rows, or a wavefront per row.
+hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
+                            const void* V, float scale, void* O, int out_dtype, hipStream_t st);
 
 // Matrix-core kernels over the tile plan: bf16 inputs, d in {64, 128}.
 hipError_t launch_rsddmm_tiles(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
@@ -68,6 +71,7 @@ hipError_t prepare_fused_mfma();
 hipError_t bounds_collect_rows(uint32_t* bits, bool clear);
 hipError_t bounds_collect_mfma(uint32_t* bits, bool clear);
 hipError_t bounds_collect_tiles(uint32_t* bits, bool clear);
+hipError_t bounds_collect_slices(uint32_t* bits, bool clear);
 // One check of `index` against [0, n) as kind `kind`, run on the device
 // (allocates and frees one int); *result = the checked index.
 hipError_t bounds_probe(int kind, int index, int n, int* result);

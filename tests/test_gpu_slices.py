@@ -1,0 +1,91 @@
+"""The 32-row slice kernels and the choice between them and their alternatives.
+
+Sizes where they can go wrong: tiles of fewer than 32 and of 33 .. 63 keys,
+gathered tiles, slices with empty tiles, a ragged last slice, more than 64
+tiles in a group, launches on both sides of the row/slice choice.  Tolerances
+as in test_gpu_parity (fp32: 1e-5 of each row's largest reference value).
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from oracle import attention as oa
+from oracle import masks as om
+
+pytestmark = pytest.mark.gpu
+
+F32_REL = 1e-5
+
+
+def _row_err(O, ref):
+    O = O.double().cpu().numpy()
+    assert np.isfinite(O).all()
+    num, den = np.abs(O - ref).max(axis=-1), np.abs(ref).max(axis=-1)
+    assert (num[den == 0] == 0).all()
+    return float((num[den > 0] / den[den > 0]).max())
+
+
+def _qkv(L, d, heads, seed, dtype="f32"):
+    w = workloads.Workload("slices", 1, heads, L, d, dtype, workloads.make_pattern("full"), 1.0, seed)
+    return workloads.make_qkv(w)
+
+
+CASES = [
+    ("full", {}, 31, 3), ("full", {}, 33, 2), ("full", {}, 97, 40), ("full", {}, 128, 16),
+    ("window", {"w": 5}, 65, 1), ("window", {"w": 16}, 700, 20), ("window", {"w": 150}, 321, 2),
+    ("blocked", {"block": 33}, 300, 12), ("dilated", {"w": 33, "dilation": 3}, 400, 12),
+    ("strided_local", {"local": 40, "stride": 33}, 500, 12),
+    ("strided_local", {"local": 4, "stride": 64}, 600, 2),
+    ("window_global", {"w": 3, "n_global": 1}, 4200, 1),
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind,params,L,heads", CASES)
+def test_fused_f32(gpu_lib, kind, params, L, heads, d):
+    splat = gpu_lib
+    print(f"[gpu] fused f32 {kind} {params} L={L} heads={heads} d={d}", flush=True)
+    Q, K, V = _qkv(L, d, heads, L + d)
+    M = om.dense_mask(kind, params, L)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    for scale in (1.0 / math.sqrt(d), -0.3, 0.0):
+        ref = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], M, scale)
+        O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+        torch.cuda.synchronize()
+        # a score's fp32 error is relative to the sum of its terms' magnitudes,
+        # which |scale| * sqrt(d) scales against the default scale
+        bound = F32_REL * max(1.0, abs(scale) * math.sqrt(d))
+        assert _row_err(O[:, :2], ref) <= bound, scale
+
+
+@pytest.mark.parametrize("where", ["K", "V"])
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+@pytest.mark.parametrize("kind,params,L,heads", [CASES[6], CASES[7], CASES[8], CASES[10]])
+def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, where):
+    """A key with an infinity or a NaN changes only the rows that have it."""
+    splat = gpu_lib
+    d, scale = 64, 0.125
+    print(f"[gpu] non-finite {where} {value} {kind} {params} L={L}", flush=True)
+    Q, K, V = _qkv(L, d, heads, 5)
+    j = L // 2
+    (K if where == "K" else V)[:, :, j, 3] = value
+    M = om.dense_mask(kind, params, L)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
+    S = splat.rsddmm(a, Qd, Kd, scale)
+    outs = {"fused": splat.sparse_mhsa_fwd(a, Qd, Kd, Vd, scale),
+            "steps": splat.rspmm(a, splat.row_softmax(a, S), Vd),
+            "unfused": splat.sparse_mhsa_unfused(a, Qd, Kd, Vd, scale)[0]}
+    torch.cuda.synchronize()
+    clean = torch.from_numpy(~M[:, j])
+    (K if where == "K" else V)[:, :, j, 3] = 0.0
+    ref = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], M, scale)
+    for name, O in outs.items():
+        O = O.cpu()
+        assert _row_err(O[:, :2, clean], ref[:, :, clean.numpy()]) <= F32_REL, name
+        if where == "V":   # the other rows: feature 3 only
+            assert not torch.isfinite(O[:, :, ~clean, 3]).any(), name
+            assert torch.isfinite(O[:, :, ~clean, 4:]).all(), name
