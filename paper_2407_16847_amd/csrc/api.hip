@@ -235,7 +235,7 @@ splat_status launch_rsddmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t
                            const void* Q, const void* K, float scale, float* S, hipStream_t st) {
   if (dtype == SPLAT_BF16)
     return launched(splat::launch_rsddmm_tiles(h->dev, B * H, d, Q, K, scale, S, st), "rsddmm");
-  return launched(splat::launch_rsddmm_rows(h->dev, dtype, B * H, d, Q, K, scale, S, st), "rsddmm");
+  return launched(splat::launch_rsddmm_f32(h->dev, B * H, d, Q, K, scale, S, st), "rsddmm");
 }
 
 bool overlap(const float* a, const float* b, size_t n) {

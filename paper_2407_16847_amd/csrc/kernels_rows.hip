@@ -4,7 +4,7 @@
 // 5.1: the k-th value of run r sits at column start + stride * k) and serve
 // every dtype and pattern: they are the fp32 path (fp32 FMA throughout, the
 // library's accurate path) and run any request the matrix-core kernels do
-// not take.  Lanes own keys (SDDMM) or output features (SpMM).
+// not take.  Lanes own output features.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -20,42 +20,6 @@ __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ void store(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store(__bf16* p, float v) { *p = (__bf16)v; }
-
-// dot(qs[0:d], row[0:d]) in fp32, sequential FMA over the features
-template <typename T>
-__device__ __forceinline__ float dot_row(const float* qs, const T* row, int d) {
-  float s = 0.f;
-  for (int c = 0; c < d; c += 4) {
-    s = fmaf(qs[c + 0], to_f32(row[c + 0]), s);
-    s = fmaf(qs[c + 1], to_f32(row[c + 1]), s);
-    s = fmaf(qs[c + 2], to_f32(row[c + 2]), s);
-    s = fmaf(qs[c + 3], to_f32(row[c + 3]), s);
-  }
-  return s;
-}
-
-template <typename T>
-__global__ __launch_bounds__(kWave) void k_rsddmm_rows(DevAcsr a, int d, const T* __restrict__ Q,
-                                                       const T* __restrict__ K, float scale,
-                                                       float* __restrict__ S) {
-  const int i = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
-  __shared__ float qs[128];
-  const size_t head = (size_t)bh * a.L * d;
-  for (int c = lane; c < d; c += kWave) qs[c] = to_f32(Q[head + (size_t)i * d + c]);
-  __syncthreads();
-  const RowRuns rr = a.runs[i];
-  float* out = S + (size_t)bh * a.nnz + a.row_ptr[i];
-  const int64_t r0 = a.row_ptr[i];   // out's position in the head
-#pragma unroll
-  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
-    const Run q = rr.r[r];
-    for (int k = lane; k < q.count; k += kWave) {
-      const int j = dbg::idx(q.start + q.stride * k, a.L, dbg::kKey);
-      out[dbg::rel(q.prefix + k, r0, a.nnz, dbg::kValue)] =
-          dot_row(qs, K + head + (size_t)j * d, d) * scale;
-    }
-  }
-}
 
 // COL: P holds the head's values in column-major order, value (i, j) at
 // col_pos(cols[j], i).
@@ -117,18 +81,6 @@ hipError_t bounds_probe(int kind, int index, int n, int* result) {
   const hipError_t f = hipFree(d);
   return e != hipSuccess ? e : f;
 #endif
-}
-
-hipError_t launch_rsddmm_rows(const DevAcsr& a, int dtype, int BH, int d, const void* Q,
-                              const void* K, float scale, float* S, hipStream_t st) {
-  dim3 grid(a.L, BH);
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_rsddmm_rows<float>, grid, dim3(kWave), 0, st, a, d, (const float*)Q,
-                       (const float*)K, scale, S);
-  else
-    hipLaunchKernelGGL(k_rsddmm_rows<__bf16>, grid, dim3(kWave), 0, st, a, d, (const __bf16*)Q,
-                       (const __bf16*)K, scale, S);
-  return hipGetLastError();
 }
 
 template <typename T, bool COL>

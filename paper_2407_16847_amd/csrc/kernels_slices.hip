@@ -36,6 +36,7 @@ constexpr int kMaxGridY = 32768;         // slices per launch dimension; more ar
 constexpr float kRefSlack = 8.f;
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------- operands
@@ -231,6 +232,44 @@ __device__ __forceinline__ void load_v(typename Mat<T, D>::V& x, const char* Vh,
       x.v[r] = *(const vrow_t*)(Vh + ((unsigned)k * RB + (unsigned)sizeof(vrow_t) * s.qi));
     }
   }
+}
+
+// f(r, present, pos) for the 16 keys of this lane: pos = the key's place
+// among the row's keys of the unit
+template <typename F>
+__device__ __forceinline__ void for_each_key(uint32_t bits, int h, F&& f) {
+  const uint32_t b = bits >> (4 * h);
+  int off = h ? __builtin_popcount(bits & 0xFu) : 0;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const uint32_t nib = (b >> (8 * g)) & 0xFu;
+    const uint32_t oth = (b >> (8 * g + 4)) & 0xFu;   // the other half's next four
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      f(4 * g + e, (nib >> e) & 1u, off + __builtin_popcount(nib & ((1u << e) - 1u)));
+    off += __builtin_popcount(nib) + __builtin_popcount(oth);
+  }
+}
+
+// number of the row's columns below x.  The quotients are below 2^18 and the
+// dividends below 2^24, so the float product is off by one at most.
+__device__ __forceinline__ int row_count_lt(const RowRuns& rr, int x) {
+  int n = 0;
+#pragma unroll
+  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
+    const Run q = rr.r[r];
+    int c = x - q.start;
+    if (q.stride != 1) {
+      const int num = c + q.stride - 1;
+      int f = (int)((float)num * __builtin_amdgcn_rcpf((float)q.stride));
+      const int rem = num - f * q.stride;
+      f += rem >= q.stride ? 1 : 0;
+      f -= rem < 0 ? 1 : 0;
+      c = c > 0 ? f : 0;
+    }
+    n += max(0, min(c, q.count));
+  }
+  return n;
 }
 
 // scores outside the row's runs set to -inf
@@ -562,6 +601,129 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
 }
 
 
+// ------------------------------------------------------------ values in ACSR
+// Where the values of a row's keys of a unit sit: position `pos` of head bh
+// on, its present keys in order.
+__device__ __forceinline__ int unit_pos(const RowRuns& rr, int row_begin, const Unit& u) {
+  return row_begin + row_count_lt(rr, u.kb);
+}
+
+// The unit's values of every row to memory.  Each row's present keys are
+// gathered in LDS and leave as row segments, eight lanes of 16 bytes a row
+// (straight from the registers a store would touch 32 rows, 32 bytes each).
+__device__ __forceinline__ void write_values(float* dst, int64_t nnz, const float (&x)[16],
+                                             uint32_t bits, const Unit& u, int pos,
+                                             const Slice& s, float* stage) {
+  // value k of row r: its 16-byte chunk k / 4 XOR-ed with r % 8 (bank conflicts)
+  auto at = [&](int r, int k) { return stage + r * kUnit + 4 * ((k >> 2) ^ (r & 7)) + (k & 3); };
+  if (u.full) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(f32x4_t*)at(s.qi, 8 * g + 4 * s.h) =
+          f32x4_t{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+  } else {
+    for_each_key(bits, s.h, [&](int r, unsigned present, int k) {
+      if (present) *at(s.qi, k) = x[r];
+    });
+  }
+  const int n = s.row_valid ? __builtin_popcount(bits) : 0;
+  const int c = 4 * (s.lane & 7);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = 8 * k + (s.lane >> 3);
+    const int nr = __shfl(n, r, 64), pr = __shfl(pos, r, 64);
+    if (c >= nr) continue;
+    const f32x4_t v = *(const f32x4_t*)at(r, c);
+    float* const p = dst + pr;
+    if (c + 4 <= nr) {
+      *(f32x4u_t*)(p + dbg::rel(c, (int64_t)pr, nnz - 3, dbg::kValue)) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (c + e < nr) p[dbg::rel(c + e, (int64_t)pr, nnz, dbg::kValue)] = v[e];
+    }
+  }
+}
+
+// ---------------------------------------------------------------- R-SDDMM
+// fp32: 32 MFMAs (d = 64) a unit against 4 KB of scores written; measured per
+// launch, a wavefront per row against this: strided+local 128, L = 2048, 12
+// heads 101 -> 21.5 us; dilated 3, L = 1000, d = 128, 8 heads 83 -> 22.3.
+// LDS: K and the staged values, at d = 128 exactly half a CU's 160 KB.
+template <typename T, int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rsddmm_slices(
+    const Group* __restrict__ groups, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
+    const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks, int L, int64_t nnz,
+    int n_slices, const T* __restrict__ Q, const T* __restrict__ K, float scale,
+    float* __restrict__ S) {
+  using M = Mat<T, D>;
+  __shared__ __attribute__((aligned(16))) float kst[kWavesPerGroup][kUnit * D * sizeof(T) / 4];
+  __shared__ __attribute__((aligned(16))) float vst[kWavesPerGroup][kWaveRows * kUnit];
+  const size_t head = (size_t)blockIdx.x * L * D;
+  const char* Kh = (const char*)(K + head);
+  float* const Sh = S + (size_t)blockIdx.x * nnz;
+  for (int sl = blockIdx.y; sl < n_slices; sl += gridDim.y) {
+    Slice s;
+    if (!s.open(sl, groups, rows, masks, L)) continue;
+    typename M::Row q;
+    load_row<T, D>(q, (const char*)(Q + head),
+                   (unsigned)s.row * (D * (unsigned)sizeof(T)) + 16u * s.h);
+    const RowRuns rr = runs[s.row];
+    const int row_begin = row_ptr[s.row];
+    Units it;
+    it.start(tiles + s.tb, s.nt, s.lane, s.wave, s.w);
+    Unit u;
+    bool more = it.next(u);
+    if (more) fetch_k<T, D>(kst[s.wave], Kh, s, u, L);
+    while (more) {
+      wait_loads();
+      typename M::Row k;
+      load_k<T, D>(k, kst[s.wave], s);
+      const uint32_t bits = s.bits(u);
+      const f32x16_t acc = M::dot(k, q);
+      Unit nu;
+      const bool next = it.next(nu);
+      if (next) fetch_k<T, D>(kst[s.wave], Kh, s, nu, L);
+      float x[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = acc[r] * scale;
+      write_values(Sh, nnz, x, bits, u, unit_pos(rr, row_begin, u), s, vst[s.wave]);
+      u = nu, more = next;
+    }
+  }
+}
+
+// The scores of a row by one wavefront, a key per lane.
+template <int D>
+__global__ __launch_bounds__(64) void k_rsddmm_rows(
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs, int L, int64_t nnz,
+    const float* __restrict__ Q, const float* __restrict__ K, float scale,
+    float* __restrict__ S) {
+  const int i = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
+  __shared__ float qs[D];
+  const size_t head = (size_t)bh * L * D;
+  for (int c = lane; c < D; c += 64) qs[c] = Q[head + (size_t)i * D + c];
+  __syncthreads();
+  const RowRuns rr = runs[i];
+  const int64_t r0 = row_ptr[i];
+  float* const out = S + (size_t)bh * nnz + r0;
+#pragma unroll
+  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
+    const Run q = rr.r[r];
+    for (int k = lane; k < q.count; k += 64) {
+      const int j = dbg::idx(q.start + q.stride * k, L, dbg::kKey);
+      const float* const key = K + head + (size_t)j * D;
+      float x = 0.f;
+#pragma unroll 8   // eight 16-byte loads in flight (all sixteen of d = 64: 2.9 us for 2.6)
+      for (int c = 0; c < D; c += 4)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x = fmaf(qs[c + e], key[c + e], x);
+      out[dbg::rel(q.prefix + k, r0, nnz, dbg::kValue)] = x * scale;
+    }
+  }
+}
+
 // --------------------------------------------------------------- launches
 // Grid: x over batch*head, so that with B*H a multiple of 8 a head's
 // workgroups share one XCD's L2; y over slices, heaviest groups first.
@@ -590,11 +752,31 @@ bool rows_faster(const DevAcsr& a, int BH, int d) {
   return rows < slc;
 }
 
+// The same for R-SDDMM (fitted to the same launches), where a wavefront per row
+// pays only while the launch is bound by latency.  Measured, rows against
+// slices: window 16, L = 256, one head 2.8 / 6.1 us, L = 4096 6.9 / 6.3;
+// strided+local 8 / 64, L = 2048, one head 5.2 / 8.6, 12 heads 36 / 17.
+bool rsddmm_rows_faster(const DevAcsr& a, int BH, int d) {
+  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
+  if (R > 4096) return false;
+  const double rows =
+      fmax(0.5e-3 * R + 0.027e-3 * w * E, 0.9 * w * ((a.max_row_nnz + 63) / 64));
+  const double slc =
+      fmax(5.5e-3 * kWavesPerGroup * a.n_groups * BH + 2.2e-6 * w * (double)a.computed * BH,
+           (w + 1) / 2 * (2.2 + 2.4 * ((a.max_slice_tiles + 1) / 2)));
+  return rows < slc;
+}
+
+// Grid of the row kernels: four rows per workgroup.
+inline dim3 row_grid(const DevAcsr& a, int BH) {
+  return dim3((unsigned)BH, (unsigned)((a.L + 3) / 4));
+}
+
 template <int D, typename OutT>
 hipError_t fused_rows(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                       float scale, void* O, hipStream_t st) {
-  hipLaunchKernelGGL((k_fused_rows<D, OutT>), dim3((unsigned)BH, (unsigned)((a.L + 3) / 4)),
-                     dim3(kThreads), 0, st, a.row_ptr, a.runs, a.L, (const float*)Q,
+  hipLaunchKernelGGL((k_fused_rows<D, OutT>), row_grid(a, BH), dim3(kThreads), 0, st,
+                     a.row_ptr, a.runs, a.L, (const float*)Q,
                      (const float*)K, (const float*)V, scale, (OutT*)O);
   return hipGetLastError();
 }
@@ -616,6 +798,20 @@ hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const
   return hipGetLastError();
 }
 
+template <typename T, int D>
+hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, float scale, float* S,
+                    hipStream_t st) {
+  if (rsddmm_rows_faster(a, BH, D)) {
+    hipLaunchKernelGGL((k_rsddmm_rows<D>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr, a.runs, a.L,
+                       a.nnz, (const float*)Q, (const float*)K, scale, S);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_rsddmm_slices<T, D>), slice_grid(a, BH), dim3(kThreads), 0, st, a.groups,
+                     a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, a.nnz, slices(a),
+                     (const T*)Q, (const T*)K, scale, S);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t bounds_collect_slices(uint32_t* bits, bool clear) { return dbg::collect(bits, clear); }
@@ -624,6 +820,12 @@ hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, cons
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st) {
   return d == 64 ? fused_d<float, 64>(a, BH, Q, K, V, scale, O, out_dtype, st)
                  : fused_d<float, 128>(a, BH, Q, K, V, scale, O, out_dtype, st);
+}
+
+hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
+                             float scale, float* S, hipStream_t st) {
+  return d == 64 ? rsddmm_d<float, 64>(a, BH, Q, K, scale, S, st)
+                 : rsddmm_d<float, 128>(a, BH, Q, K, scale, S, st);
 }
 
 }  // namespace splat

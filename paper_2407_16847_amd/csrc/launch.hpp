@@ -37,8 +37,6 @@ __device__ __forceinline__ int col_pos(const ColRun& c, int row) {
 // dtype / out dtype: 0 = fp32, 1 = bf16.
 
 // Row-per-wave kernels: any d in {64, 128}, both dtypes.
-hipError_t launch_rsddmm_rows(const DevAcsr& a, int dtype, int BH, int d, const void* Q,
-                              const void* K, float scale, float* S, hipStream_t st);
 // colmajor: P holds the column-major values (requires a.cols).
 hipError_t launch_rspmm_rows(const DevAcsr& a, int dtype, int BH, int d, const float* P,
                              const void* V, void* O, int out_dtype, bool colmajor, hipStream_t st);
@@ -46,6 +44,8 @@ hipError_t launch_rspmm_rows(const DevAcsr& a, int dtype, int BH, int d, const f
 // fp32: on the matrix cores, a workgroup per 32 rows, or a wavefront per row.
 hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st);
+hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
+                             float scale, float* S, hipStream_t st);
 
 // Matrix-core kernels over the tile plan: bf16 inputs, d in {64, 128}.
 hipError_t launch_rsddmm_tiles(const DevAcsr& a, int BH, int d, const void* Q, const void* K,

@@ -89,3 +89,25 @@ def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, wh
         if where == "V":   # the other rows: feature 3 only
             assert not torch.isfinite(O[:, :, ~clean, 3]).any(), name
             assert torch.isfinite(O[:, :, ~clean, 4:]).all(), name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind,params,L,heads", CASES)
+def test_steps_f32(gpu_lib, kind, params, L, heads, d):
+    splat = gpu_lib
+    print(f"[gpu] steps f32 {kind} {params} L={L} heads={heads} d={d}", flush=True)
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = _qkv(L, d, heads, L + 2 * d)
+    M = om.dense_mask(kind, params, L)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    S = splat.rsddmm(a, Q.cuda(), K.cuda(), scale)
+    P = splat.row_softmax(a, S)
+    O = splat.rspmm(a, P, V.cuda())
+    torch.cuda.synchronize()
+    ref, _, _ = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], M, scale, want_csr=True)
+    assert _row_err(O[:, :2], ref) <= F32_REL
+    m = torch.from_numpy(M)
+    for h in (0, heads - 1):
+        x = Q[0, h].double() @ K[0, h].double().t() * scale
+        mag = Q[0, h].double().abs() @ K[0, h].double().abs().t() * scale
+        assert float(((S[0, h].cpu().double() - x[m]).abs() / mag[m]).max()) <= F32_REL
