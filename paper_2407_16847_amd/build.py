@@ -26,7 +26,7 @@ OUT_CHECKED = os.path.join(HERE, "libsplat_checked.so")
 BUILD_DIR_CHECKED = os.path.join(HERE, "_build_checked")
 ARCH = "gfx950"
 
-SOURCES = ["acsr_host.cpp", "tiling.cpp", "api.hip", "kernels_rows.hip", "kernels_mfma.hip", "kernels_tiles.hip",
+SOURCES = ["acsr_host.cpp", "tiling.cpp", "api.hip", "kernels_mfma.hip", "kernels_tiles.hip",
            "kernels_slices.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unknown-pragmas"]

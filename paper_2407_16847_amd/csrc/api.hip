@@ -228,7 +228,7 @@ splat_status launch_rspmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t 
     return launched(splat::launch_rspmm_tiles(h->dev, B * H, d, P, V, O, out_dtype, colmajor, st),
                     "rspmm");
   return launched(
-      splat::launch_rspmm_rows(h->dev, dtype, B * H, d, P, V, O, out_dtype, colmajor, st), "rspmm");
+      splat::launch_rspmm_f32(h->dev, B * H, d, P, V, O, out_dtype, colmajor, st), "rspmm");
 }
 
 splat_status launch_rsddmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
@@ -615,7 +615,6 @@ splat_status splat_debug_bounds(uint32_t* flags, int32_t clear) {
 #else
   uint32_t bits = 0;
   hipError_t e = hipDeviceSynchronize();
-  if (e == hipSuccess) e = splat::bounds_collect_rows(&bits, clear != 0);
   if (e == hipSuccess) e = splat::bounds_collect_mfma(&bits, clear != 0);
   if (e == hipSuccess) e = splat::bounds_collect_tiles(&bits, clear != 0);
   if (e == hipSuccess) e = splat::bounds_collect_slices(&bits, clear != 0);

@@ -724,6 +724,155 @@ __global__ __launch_bounds__(64) void k_rsddmm_rows(
   }
 }
 
+// ----------------------------------------------------------------- R-SpMM
+// COL: P holds the head's values in column-major order, value (i, j) at
+// col_pos(cols[j], i).  fp32, a wavefront per row against slices: strided+local
+// 128, L = 2048, 12 heads 54 -> 20.6 us; dilated 3, L = 1000, d = 128, 8 heads
+// 64 -> 20.6; per unit 32 MFMAs (d = 64) and V's 8 KB against P's 4 KB.
+
+// O of row i by one wavefront, lanes over the features.
+template <int D, typename OutT, bool COL>
+__device__ __forceinline__ void spmm_row(int i, int lane, const RowRuns* runs,
+                                         const int32_t* row_ptr, const ColRun* cols, int L,
+                                         int64_t nnz, const float* Ph, const float* Vh, OutT* Oh) {
+  constexpr int NC = D / 64;
+  const RowRuns rr = runs[i];
+  const int64_t r0 = COL ? 0 : row_ptr[i];   // p's position in the head
+  const float* const p = Ph + r0;
+  float acc[NC];
+#pragma unroll
+  for (int b = 0; b < NC; ++b) acc[b] = 0.f;
+#pragma unroll
+  for (int r = 0; r < SPLAT_MAX_RUNS; ++r) {
+    const Run q = rr.r[r];
+    auto key = [&](int k) {
+      const int j = dbg::idx(q.start + q.stride * k, L, dbg::kKey);
+      const float pk = COL ? p[dbg::idx((int64_t)col_pos(cols[j], i), nnz, dbg::kColPos)]
+                           : p[dbg::rel(q.prefix + k, r0, nnz, dbg::kValue)];
+      const float* const v = Vh + (size_t)j * D;
+#pragma unroll
+      for (int b = 0; b < NC; ++b) acc[b] = fmaf(pk, v[64 * b + lane], acc[b]);
+    };
+    int k = 0;   // eight loads in flight (four: up to 1.3 times longer on long rows)
+#pragma unroll 1
+    for (; k + 8 <= q.count; k += 8)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) key(k + e);
+    if (k + 4 <= q.count) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key(k + e);
+      k += 4;
+    }
+#pragma unroll 1
+    for (; k < q.count; ++k) key(k);
+  }
+#pragma unroll
+  for (int b = 0; b < NC; ++b) store1(Oh + (size_t)i * D + 64 * b + lane, acc[b]);
+}
+
+template <int D, typename OutT, bool COL>
+__global__ __launch_bounds__(64) void k_rspmm_rows(
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
+    const ColRun* __restrict__ cols, int L, int64_t nnz, const float* __restrict__ P,
+    const float* __restrict__ V, OutT* __restrict__ O) {
+  const size_t head = (size_t)blockIdx.y * L * D;
+  spmm_row<D, OutT, COL>(blockIdx.x, threadIdx.x, runs, row_ptr, cols, L, nnz,
+                         P + (size_t)blockIdx.y * nnz, V + head, O + head);
+}
+
+template <typename T, int D, typename OutT, bool COL>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
+    const Group* __restrict__ groups, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
+    const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks,
+    const ColRun* __restrict__ cols, int L, int64_t nnz, int n_slices,
+    const float* __restrict__ P, const T* __restrict__ V, OutT* __restrict__ O) {
+  using M = Mat<T, D>;
+  constexpr int NB = D / 32;
+  __shared__ __attribute__((aligned(16))) Shared<D> sh;
+  const size_t head = (size_t)blockIdx.x * L * D;
+  const char* Vh = (const char*)(V + head);
+  const float* const Ph = P + (size_t)blockIdx.x * nnz;
+  for (int sl = blockIdx.y; sl < n_slices; sl += gridDim.y) {
+    Slice s;
+    if (!s.open(sl, groups, rows, masks, L)) continue;
+    RowRuns rr;
+    if (!COL) rr = runs[s.row];
+    const int row_begin = row_ptr[s.row];
+    f32x16_t o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    float z = 0.f;
+    if (threadIdx.x == 0) sh.redo = 0;
+    Units it;
+    it.start(tiles + s.tb, s.nt, s.lane, s.wave, s.w);
+    Unit u;
+    while (it.next(u)) {
+      typename M::V v0, v1;
+      load_v<T, D>(v0, Vh, s, u, 0, L);
+      load_v<T, D>(v1, Vh, s, u, 1, L);
+      const uint32_t bits = s.row_valid ? s.bits(u) : 0u;
+      float p[16];
+      if (COL) {
+        const uint32_t b = bits >> (4 * s.h);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = s.key(u, 8 * (r >> 2) + 4 * s.h + (r & 3), L);
+          p[r] = (b >> (8 * (r >> 2) + (r & 3))) & 1u
+                     ? Ph[dbg::idx((int64_t)col_pos(cols[j], s.row), nnz, dbg::kColPos)]
+                     : 0.f;
+        }
+      } else {
+        const int pos = unit_pos(rr, row_begin, u);
+        const float* src = Ph + pos;
+        if (u.full && s.row_valid) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4u_t a = *(const f32x4u_t*)(src + dbg::rel(8 * g + 4 * s.h, (int64_t)pos,
+                                                                 nnz - 3, dbg::kValue));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[4 * g + e] = a[e];
+          }
+        } else {
+          for_each_key(bits, s.h, [&](int r, unsigned present, int k) {
+            p[r] = present ? src[dbg::rel(k, (int64_t)pos, nnz, dbg::kValue)] : 0.f;
+          });
+        }
+      }
+      check_v<T, D>(z, v0, u);
+      M::pv(o, v0, p, 0);
+      check_v<T, D>(z, v1, u);
+      M::pv(o, v1, p, 1);
+    }
+    if constexpr (std::is_same<T, float>::value) {
+      __syncthreads();
+      if (z != z) sh.redo = 1;
+      __syncthreads();
+      if (sh.redo) {
+        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
+          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
+          if (i >= 0)
+            spmm_row<D, OutT, COL>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+        }
+        __syncthreads();
+        continue;
+      }
+    }
+    combine<D, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
+    __syncthreads();   // LDS is reused by the next slice
+  }
+}
+
+#ifdef SPLAT_DEBUG_BOUNDS
+// One index check on the device (the checked build's own test): out = the
+// checked index.
+__global__ void k_bounds_probe(int kind, int index, int n, int* out) {
+  *out = dbg::idx(index, n, (dbg::Kind)kind);
+}
+#endif
+
 // --------------------------------------------------------------- launches
 // Grid: x over batch*head, so that with B*H a multiple of 8 a head's
 // workgroups share one XCD's L2; y over slices, heaviest groups first.
@@ -763,6 +912,20 @@ bool rsddmm_rows_faster(const DevAcsr& a, int BH, int d) {
       fmax(0.5e-3 * R + 0.027e-3 * w * E, 0.9 * w * ((a.max_row_nnz + 63) / 64));
   const double slc =
       fmax(5.5e-3 * kWavesPerGroup * a.n_groups * BH + 2.2e-6 * w * (double)a.computed * BH,
+           (w + 1) / 2 * (2.2 + 2.4 * ((a.max_slice_tiles + 1) / 2)));
+  return rows < slc;
+}
+
+// And for R-SpMM, where a wavefront per row reads V and P in whole lines and
+// pays over a wider range.  Measured, rows against slices: window 16, L = 256,
+// one head 3.1 / 6.1 us; strided+local 8 / 64, L = 2048, 12 heads 14.6 / 16.5;
+// strided+local 128, L = 2048, 12 heads 36.5 / 20.6; full, L = 128, d = 128, 4
+// heads 5.6 / 7.2.
+bool rspmm_rows_faster(const DevAcsr& a, int BH, int d) {
+  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
+  const double rows = fmax(0.25e-3 * R + 0.0085e-3 * w * E, 0.022 * w * a.max_row_nnz);
+  const double slc =
+      fmax(7.5e-3 * kWavesPerGroup * a.n_groups * BH + 2.2e-6 * w * (double)a.computed * BH,
            (w + 1) / 2 * (2.2 + 2.4 * ((a.max_slice_tiles + 1) / 2)));
   return rows < slc;
 }
@@ -812,9 +975,52 @@ hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, floa
   return hipGetLastError();
 }
 
+template <typename T, int D, typename OutT, bool COL>
+hipError_t rspmm_d(const DevAcsr& a, int BH, const float* P, const void* V, void* O,
+                   hipStream_t st) {
+  if (rspmm_rows_faster(a, BH, D)) {
+    hipLaunchKernelGGL((k_rspmm_rows<D, OutT, COL>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr,
+                       a.runs, a.cols, a.L, a.nnz, P, (const float*)V, (OutT*)O);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_rspmm_slices<T, D, OutT, COL>), slice_grid(a, BH), dim3(kThreads), 0, st,
+                     a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.cols, a.L, a.nnz,
+                     slices(a), P, (const T*)V, (OutT*)O);
+  return hipGetLastError();
+}
+
+template <typename T, bool COL>
+hipError_t rspmm_t(const DevAcsr& a, int BH, int d, const float* P, const void* V, void* O,
+                   int out_dtype, hipStream_t st) {
+  if (d == 64)
+    return out_dtype == 0 ? rspmm_d<T, 64, float, COL>(a, BH, P, V, O, st)
+                          : rspmm_d<T, 64, __bf16, COL>(a, BH, P, V, O, st);
+  return out_dtype == 0 ? rspmm_d<T, 128, float, COL>(a, BH, P, V, O, st)
+                        : rspmm_d<T, 128, __bf16, COL>(a, BH, P, V, O, st);
+}
+
 }  // namespace
 
 hipError_t bounds_collect_slices(uint32_t* bits, bool clear) { return dbg::collect(bits, clear); }
+
+hipError_t bounds_probe(int kind, int index, int n, int* result) {
+#ifndef SPLAT_DEBUG_BOUNDS
+  (void)kind;
+  (void)index;
+  (void)n;
+  (void)result;
+  return hipErrorNotSupported;
+#else
+  int* d = nullptr;
+  hipError_t e = hipMalloc(&d, sizeof(int));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_bounds_probe, dim3(1), dim3(1), 0, 0, kind, index, n, d);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpy(result, d, sizeof(int), hipMemcpyDeviceToHost);
+  const hipError_t f = hipFree(d);
+  return e != hipSuccess ? e : f;
+#endif
+}
 
 hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st) {
@@ -826,6 +1032,12 @@ hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, con
                              float scale, float* S, hipStream_t st) {
   return d == 64 ? rsddmm_d<float, 64>(a, BH, Q, K, scale, S, st)
                  : rsddmm_d<float, 128>(a, BH, Q, K, scale, S, st);
+}
+
+hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, const void* V,
+                            void* O, int out_dtype, bool colmajor, hipStream_t st) {
+  return colmajor ? rspmm_t<float, true>(a, BH, d, P, V, O, out_dtype, st)
+                  : rspmm_t<float, false>(a, BH, d, P, V, O, out_dtype, st);
 }
 
 }  // namespace splat

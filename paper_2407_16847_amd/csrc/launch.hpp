@@ -36,16 +36,14 @@ __device__ __forceinline__ int col_pos(const ColRun& c, int row) {
 // Every launcher enqueues on `st` and returns the launch status.
 // dtype / out dtype: 0 = fp32, 1 = bf16.
 
-// Row-per-wave kernels: any d in {64, 128}, both dtypes.
-// colmajor: P holds the column-major values (requires a.cols).
-hipError_t launch_rspmm_rows(const DevAcsr& a, int dtype, int BH, int d, const float* P,
-                             const void* V, void* O, int out_dtype, bool colmajor, hipStream_t st);
-
 // fp32: on the matrix cores, a workgroup per 32 rows, or a wavefront per row.
 hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st);
 hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                              float scale, float* S, hipStream_t st);
+// colmajor: P holds the column-major values (requires a.cols).
+hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, const void* V,
+                            void* O, int out_dtype, bool colmajor, hipStream_t st);
 
 // Matrix-core kernels over the tile plan: bf16 inputs, d in {64, 128}.
 hipError_t launch_rsddmm_tiles(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
@@ -68,7 +66,6 @@ hipError_t prepare_fused_mfma();
 // Index checks of a build with -DSPLAT_DEBUG_BOUNDS (no-ops otherwise): each
 // kernel file's flags on the current device, OR-ed into *bits (bit k = kind
 // k of bounds.hpp), cleared when `clear`.
-hipError_t bounds_collect_rows(uint32_t* bits, bool clear);
 hipError_t bounds_collect_mfma(uint32_t* bits, bool clear);
 hipError_t bounds_collect_tiles(uint32_t* bits, bool clear);
 hipError_t bounds_collect_slices(uint32_t* bits, bool clear);
