@@ -355,7 +355,9 @@ splat_status splat_rspmm_colmajor(splat_acsr_t h, splat_dtype dtype, int32_t B, 
  * transposes.  S: fp32 [B,H,nnz] workspace (holds P afterwards); Pt: fp32
  * [B,H,nnz] workspace, used (and required non-NULL) only on the column-major
  * branch.  *used_colmajor (if non-NULL) is set to 1 on the column-major
- * branch, 0 otherwise.  Results as the individual calls.
+ * branch, 0 otherwise.  Results as the individual calls' (within their
+ * rounding: one kernel may form P and O without storing S first; S then holds
+ * P, and Pt its column-major copy, as after the individual calls).
  */
 #define SPLAT_DENSE_ALPHA 0.10f
 splat_status splat_sparse_mhsa_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H,
@@ -367,8 +369,8 @@ splat_status splat_sparse_mhsa_unfused(splat_acsr_t h, splat_dtype dtype, int32_
 /*
  * splat_sparse_mhsa_unfused_noalloc -- splat_sparse_mhsa_unfused for callers
  * that cannot allocate device memory (code under HIP graph capture, tight
- * serving loops, harnesses that forbid allocation): the same chain, the same
- * kernels and the same results, with S (and, on the column-major branch,
+ * serving loops, harnesses that forbid allocation): the same chain and the
+ * same results, with S (and, on the column-major branch,
  * Pt) held in a scratch array inside the library instead of caller
  * workspaces.  The caller passes Q, K, V and O as for
  * splat_sparse_mhsa_unfused; the call allocates nothing.

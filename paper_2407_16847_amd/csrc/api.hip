@@ -263,6 +263,42 @@ bool use_colmajor(const HostAcsr& a, float alpha) {
   return a.col_regular == 1 && a.nnz > 0 && density >= (double)alpha;
 }
 
+// The unfused chain.  keep_values: the caller reads P in S (and Pt) afterwards;
+// without it a bf16 chain that runs as one kernel leaves them alone.
+splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
+                         const void* Q, const void* K, const void* V, float scale, float* S,
+                         float* Pt, void* O, splat_dtype out_dtype, float alpha,
+                         int32_t* used_colmajor, hipStream_t st, bool keep_values) {
+  CHECK(check_handle(h, B, H));
+  const HostAcsr& a = h->host;
+  // the paper's density analysis: dense masks take the column-major layout
+  const bool col = use_colmajor(a, alpha);
+  // every step is validated before anything is enqueued
+  CHECK(check_dtype(dtype, "dtype"));
+  CHECK(check_d(d));
+  CHECK(check_ptr(Q, "Q"));
+  CHECK(check_ptr(K, "K"));
+  CHECK(check_rspmm(h, dtype, B, H, d, S, V, O, out_dtype, false));
+  if (col) CHECK(check_transpose(h, B, H, S, Pt));
+  if (splat::chain_faster(h->dev, dtype, B * H, d)) {
+    const bool values = keep_values || dtype != SPLAT_BF16;
+    if (used_colmajor) *used_colmajor = col ? 1 : 0;
+    return launched(splat::launch_chain(h->dev, dtype, B * H, d, Q, K, V, scale,
+                                        values ? S : nullptr, values && col ? Pt : nullptr, O,
+                                        out_dtype, st),
+                    "sparse_mhsa_unfused");
+  }
+  if (a.nnz > 0) {
+    CHECK(launch_rsddmm(h, dtype, B, H, d, Q, K, scale, S, st));
+    CHECK(launched(splat::launch_softmax(h->dev, B * H, S, S, st), "row_softmax"));
+    if (col)
+      CHECK(launched(splat::launch_transpose_colmajor(h->dev, B * H, S, Pt, st),
+                     "transpose_colmajor"));
+  }
+  if (used_colmajor) *used_colmajor = col ? 1 : 0;
+  return launch_rspmm(h, dtype, B, H, d, col ? Pt : S, V, O, out_dtype, col, st);
+}
+
 // Scratch of splat_sparse_mhsa_unfused_noalloc: the S values and, on the
 // column-major branch, their transposed copy.  Every GPU the library runs on
 // holds its own copy for the life of the process.  In host code `scratch`
@@ -561,27 +597,8 @@ splat_status splat_sparse_mhsa_unfused(splat_acsr_t h, splat_dtype dtype, int32_
                                        float scale, float* S, float* Pt, void* O,
                                        splat_dtype out_dtype, float alpha, int32_t* used_colmajor,
                                        void* stream) {
-  CHECK(check_handle(h, B, H));
-  const HostAcsr& a = h->host;
-  // the paper's density analysis: dense masks take the column-major layout
-  const bool col = use_colmajor(a, alpha);
-  // every step is validated before anything is enqueued
-  CHECK(check_dtype(dtype, "dtype"));
-  CHECK(check_d(d));
-  CHECK(check_ptr(Q, "Q"));
-  CHECK(check_ptr(K, "K"));
-  CHECK(check_rspmm(h, dtype, B, H, d, S, V, O, out_dtype, false));
-  if (col) CHECK(check_transpose(h, B, H, S, Pt));
-  hipStream_t st = (hipStream_t)stream;
-  if (a.nnz > 0) {
-    CHECK(launch_rsddmm(h, dtype, B, H, d, Q, K, scale, S, st));
-    CHECK(launched(splat::launch_softmax(h->dev, B * H, S, S, st), "row_softmax"));
-    if (col)
-      CHECK(launched(splat::launch_transpose_colmajor(h->dev, B * H, S, Pt, st),
-                     "transpose_colmajor"));
-  }
-  if (used_colmajor) *used_colmajor = col ? 1 : 0;
-  return launch_rspmm(h, dtype, B, H, d, col ? Pt : S, V, O, out_dtype, col, st);
+  return run_unfused(h, dtype, B, H, d, Q, K, V, scale, S, Pt, O, out_dtype, alpha, used_colmajor,
+                     (hipStream_t)stream, true);
 }
 
 splat_status splat_sparse_mhsa_unfused_noalloc(splat_acsr_t h, splat_dtype dtype, int32_t B,
@@ -602,9 +619,9 @@ splat_status splat_sparse_mhsa_unfused_noalloc(splat_acsr_t h, splat_dtype dtype
                 need, col ? ", twice for the column-major layout" : "", kScratchBytes);
   char* base = nullptr;
   CHECK(scratch_on(h->device, &base));
-  return splat_sparse_mhsa_unfused(h, dtype, B, H, d, Q, K, V, scale, (float*)base,
-                                   col ? (float*)(base + s_bytes) : nullptr, O, out_dtype, alpha,
-                                   used_colmajor, stream);
+  return run_unfused(h, dtype, B, H, d, Q, K, V, scale, (float*)base,
+                     col ? (float*)(base + s_bytes) : nullptr, O, out_dtype, alpha, used_colmajor,
+                     (hipStream_t)stream, false);
 }
 
 splat_status splat_debug_bounds(uint32_t* flags, int32_t clear) {

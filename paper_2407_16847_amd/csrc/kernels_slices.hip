@@ -38,6 +38,7 @@ constexpr float kRefSlack = 8.f;
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------- operands
 template <typename T, int D>
@@ -72,6 +73,58 @@ struct Mat<float, D> {
 #pragma unroll
       for (int b = 0; b < NB; ++b)
         o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.v[r][b], p[8 * j + r], o[b], 0, 0, 0);
+  }
+};
+
+// bf16: v_mfma_f32_32x32x16_bf16
+template <int D>
+struct Mat<__bf16, D> {
+  static constexpr int NB = D / 32;
+  typedef typename std::conditional<NB == 2, unsigned, u32x2_t>::type vrow_t;
+  struct Row {               // features 16 t + 8 h .. + 7 of a Q or K row
+    bf16x8_t v[D / 16];
+  };
+  struct V {                 // features NB i .. of 8 key rows: half j of a unit
+    vrow_t v[8];
+  };
+  static __device__ __forceinline__ f32x16_t dot(const Row& k, const Row& q) {
+    f32x16_t s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) s = mfma32(k.v[t], q.v[t], s);
+    return s;
+  }
+  // block b's operand of the half's k-step: element e is key row e
+  static __device__ __forceinline__ bf16x8_t vt(const V& v, int b) {
+    u32x4_t a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      unsigned x, y;
+      if constexpr (NB == 2) {
+        x = v.v[2 * e], y = v.v[2 * e + 1];
+      } else {
+        x = v.v[2 * e][b >> 1], y = v.v[2 * e + 1][b >> 1];
+      }
+      a[e] = __builtin_amdgcn_perm(y, x, (b & 1) ? 0x07060302u : 0x05040100u);
+    }
+    return __builtin_bit_cast(bf16x8_t, a);
+  }
+  // P as a bf16 high part plus a bf16 remainder: about 16 significant bits
+  static __device__ __forceinline__ void pv(f32x16_t (&o)[NB], const V& v, const float (&p)[16],
+                                            int j) {
+    bf16x8_t hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      hi[e] = (__bf16)p[8 * j + e];
+      lo[e] = (__bf16)(p[8 * j + e] - (float)hi[e]);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const bf16x8_t a = vt(v, b);
+      o[b] = mfma32(a, hi, o[b]);
+      o[b] = mfma32(a, lo, o[b]);
+    }
   }
 };
 
@@ -179,9 +232,11 @@ struct Slice {
 // rows per load, and from there into the operand: loaded straight into the
 // operand, each load would touch 32 rows, 32 bytes of each, and K would hold
 // registers a unit ahead (d = 128: 862 us against 631, full mask, L = 2048,
-// 32 heads).  The 16-byte chunks of row r sit XOR-ed with r % 16, so that the
-// operand reads (16 lanes, 16 rows) are free of bank conflicts.  Keys past the
-// unit's end re-read its last.
+// 32 heads).  The 16-byte chunks of row r sit XOR-ed with r % 16 (128-byte rows:
+// r / 2 % 8), so that the operand reads (16 lanes, 16 rows) are free of bank
+// conflicts.  Keys past the unit's end re-read its last.
+template <int CPR>
+__device__ __forceinline__ int swz_row(int r) { return CPR == 8 ? (r >> 1) & 7 : r & 15; }
 template <typename T, int D>
 __device__ __forceinline__ void fetch_k(float* stage, const char* Kh, const Slice& s, const Unit& u,
                                         int L) {
@@ -189,7 +244,7 @@ __device__ __forceinline__ void fetch_k(float* stage, const char* Kh, const Slic
 #pragma unroll
   for (int k = 0; k < kUnit / RPL; ++k) {
     const int r = RPL * k + s.lane / CPR;
-    const int c = (s.lane % CPR) ^ (r & 15);
+    const int c = (s.lane % CPR) ^ swz_row<CPR>(r);
     dma16(Kh + ((unsigned)s.key(u, r, L) * (unsigned)RB + 16u * c), (char*)stage + kDmaBlock * k);
   }
 }
@@ -197,7 +252,7 @@ template <typename T, int D>
 __device__ __forceinline__ void load_k(typename Mat<T, D>::Row& x, const float* stage,
                                        const Slice& s) {
   constexpr int RB = D * (int)sizeof(T);
-  const int off = s.qi * RB + 16 * (s.h ^ (s.qi & 15));
+  const int off = s.qi * RB + 16 * (s.h ^ swz_row<RB / 16>(s.qi));
 #pragma unroll
   for (int t = 0; t < RB / 32; ++t)
     x.v[t] = *(const typename std::remove_reference<decltype(x.v[0])>::type*)((const char*)stage +
@@ -344,6 +399,15 @@ __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 3
       store_o4<OutT>(orow + c, v * f);
     }
   }
+}
+
+// exp(x - m) as the row softmax forms it
+__device__ __forceinline__ float exp_from(float x, float m) {
+  return exp2_hw((x - m) * 1.4426950408889634f);
+}
+// the factor that takes a sum from reference m to mt >= m (-inf: nothing summed)
+__device__ __forceinline__ float rescale(float m, float mt) {
+  return m == -INFINITY ? 0.f : exp_from(m, mt);
 }
 
 // ---------------------------------------------------------- one row, VALU
@@ -645,6 +709,41 @@ __device__ __forceinline__ void write_values(float* dst, int64_t nnz, const floa
   }
 }
 
+// The unit's values to their column-major places.  A register holds one key of
+// 32 rows, neighbours in the column: its store covers 128 bytes of it (of two,
+// one per half).  Lane i reads key i's descriptor; where every column steps by
+// one row, as in all but dilated masks, a value's place is (ptr - start) + row.
+__device__ __forceinline__ void write_columns(float* dst, int64_t nnz, const float (&x)[16],
+                                              uint32_t bits, const Unit& u, const ColRun* cols,
+                                              const Slice& s, int L, float* stage) {
+  const ColRun mine = cols[s.key(u, s.qi, L)];
+  const uint32_t b = bits >> (4 * s.h);
+  if (__all(mine.stride == 1)) {
+    int* const base = (int*)stage;
+    base[s.qi] = mine.ptr - mine.start;
+    wait_lds();
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int4 c = *(const int4*)(base + 8 * g + 4 * s.h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((b >> (8 * g + e)) & 1u) {
+          // the column-wise analysis ends at 2^28 values a head: 32-bit offsets
+          const int at = dbg::idx((&c.x)[e] + s.row, (int)nnz, dbg::kColPos);
+          *(float*)((char*)dst + 4u * (unsigned)at) = x[4 * g + e];
+        }
+    }
+    wait_lds();
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int k = 8 * (r >> 2) + (r & 3);
+    const ColRun c = cols[s.key(u, k + 4 * s.h, L)];
+    if ((b >> k) & 1u) dst[dbg::idx((int64_t)col_pos(c, s.row), nnz, dbg::kColPos)] = x[r];
+  }
+}
+
 // ---------------------------------------------------------------- R-SDDMM
 // fp32: 32 MFMAs (d = 64) a unit against 4 KB of scores written; measured per
 // launch, a wavefront per row against this: strided+local 128, L = 2048, 12
@@ -865,6 +964,174 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
   }
 }
 
+// ------------------------------------------------------- the unfused chain
+// P = softmax_nz(scale * M (x) Q K^T) and O = P V in one kernel: P is written
+// once and never read back.  Pass 1 forms each row's maximum and sum over its
+// units (per lane; halves and wavefronts combined at the end), pass 2 forms the
+// scores again -- the first unit's are kept -- and from them P and O.  The
+// values are those of the single steps: fp32 scores, the exact maximum, P in
+// fp32; with bf16 V the products take P as a bf16 high part plus a remainder.
+// OUT: 0 = O alone, 1 = O and P, 2 = O, P and the column-major copy Pt.
+//
+// Bound by the stores of P at large sizes (window 512 + 64 global, L = 4096, 64
+// heads, 1.1 GB of P: 569 us against 1006 for three launches that store S, read
+// it, store P and read it), by the dependent loads of one slice at small ones
+// (blocked 64, L = 1024, 16 heads: 7.1 us with O alone, 9.9 with P, 26.5 for
+// three launches).  Window 128, L = 1024, 64 heads: 45 us with P, 57 with Pt as
+// well (134 for four launches).  Registers: three wavefronts per SIMD at bf16,
+// d = 64 (two: 53 us against 45 with P, window 128), two elsewhere (three: 159
+// us against 101, dilated 2, L = 4096, d = 128).
+template <typename T, int D, typename OutT, int OUT>
+__global__ __launch_bounds__(kThreads, D == 64 && sizeof(T) == 2 ? 3 : 2) void k_chain_slices(
+    const Group* __restrict__ groups, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
+    const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks,
+    const ColRun* __restrict__ cols, int L, int64_t nnz, int n_slices, const T* __restrict__ Q,
+    const T* __restrict__ K, const T* __restrict__ V, float scale, float* P, float* Pt,
+    OutT* __restrict__ O) {
+  using M = Mat<T, D>;
+  constexpr bool kF32 = std::is_same<T, float>::value;
+  constexpr int NB = D / 32;
+  constexpr int KF = kUnit * D * (int)sizeof(T) / 4;   // floats of a staged K unit
+  __shared__ __attribute__((aligned(16))) Shared<D> sh;
+  // values on their way to P: beside K in the wavefront's part of sh.o where
+  // both fit (bf16), apart from it otherwise
+  constexpr bool kApart = KF + kWaveRows * kUnit > kWaveRows * Shared<D>::OS;
+  __shared__ __attribute__((aligned(16))) float apart[kApart ? kWavesPerGroup : 1]
+                                                     [kApart ? kWaveRows * kUnit : 4];
+  __shared__ RowRuns rrs[OUT ? kWaveRows : 1];
+  const size_t head = (size_t)blockIdx.x * L * D;
+  const char* Kh = (const char*)(K + head);
+  const char* Vh = (const char*)(V + head);
+  float* const Ph = P + (size_t)blockIdx.x * nnz;
+  for (int sl = blockIdx.y; sl < n_slices; sl += gridDim.y) {
+    Slice s;
+    if (!s.open(sl, groups, rows, masks, L)) continue;
+    float* const kst = sh.o[s.wave];
+    float* const vst = kApart ? apart[s.wave] : kst + KF;
+    typename M::Row q, k;
+    load_row<T, D>(q, (const char*)(Q + head),
+                   (unsigned)s.row * (D * (unsigned)sizeof(T)) + 16u * s.h);
+    // the rows' runs wait in LDS: they would hold 16 registers a lane
+    int row_begin = 0;
+    if (OUT) {
+      row_begin = row_ptr[s.row];
+      if (threadIdx.x < kWaveRows) rrs[s.qi] = runs[s.row];
+    }
+    if (threadIdx.x == 0) sh.redo = 0;
+
+    Units it;
+    Unit u, nu;
+    it.start(tiles + s.tb, s.nt, s.lane, s.wave, s.w);
+    bool more = it.next(u), kept = false;
+    if (more) fetch_k<T, D>(kst, Kh, s, u, L);
+    f32x16_t acc0;
+    float m = -INFINITY, l = 0.f;
+    while (more) {
+      const uint32_t bits = s.bits(u);
+      wait_loads();
+      load_k<T, D>(k, kst, s);
+      const f32x16_t acc = M::dot(k, q);
+      if (!kept) acc0 = acc, kept = true;
+      const bool next = it.next(nu);
+      if (next) fetch_k<T, D>(kst, Kh, s, nu, L);
+      float x[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = acc[r] * scale;
+      if (!u.full) mask_unit(x, bits, s.h);
+      float mx = m;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, x[r]);
+      const float mu = mx == -INFINITY ? 0.f : mx;   // no key yet: exp(-inf - 0) = 0
+      l *= m == -INFINITY ? 0.f : exp_from(m, mu);
+      m = mx;
+      float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) l0 += exp_from(x[r], mu), l1 += exp_from(x[r + 1], mu);
+      l += l0 + l1;
+      u = nu, more = next;
+    }
+    {
+      const float mo = lane_xor32(m), lo = lane_xor32(l), mt = fmaxf(m, mo);
+      l = l * rescale(m, mt) + lo * rescale(mo, mt);
+      m = mt;
+    }
+    if (s.h == 0) sh.m[s.wave][s.qi] = m, sh.l[s.wave][s.qi] = l;
+    // the second pass's first units, under the barrier
+    it.start(tiles + s.tb, s.nt, s.lane, s.wave, s.w);
+    more = it.next(u);
+    bool next = more && it.next(nu);
+    if (next) fetch_k<T, D>(kst, Kh, s, nu, L);
+    __syncthreads();
+    float mt = -INFINITY, lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) mt = fmaxf(mt, sh.m[w][s.qi]);
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) lt += sh.l[w][s.qi] * rescale(sh.m[w][s.qi], mt);
+    const float mu = mt == -INFINITY ? 0.f : mt, inv = 1.f / lt;
+
+    f32x16_t o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    float z = 0.f;
+    while (more) {
+      typename M::V v0, v1;
+      load_v<T, D>(v0, Vh, s, u, 0, L);
+      if (kF32 && D == 64) load_v<T, D>(v1, Vh, s, u, 1, L);
+      const uint32_t bits = s.bits(u);
+      float p[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[r] = exp_from(acc0[r] * scale, mu) * inv;
+      if (!u.full) {   // 0 where the row lacks the key
+        const unsigned word = bits >> (4 * s.h);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          p[r] = __builtin_bit_cast(
+              float, __builtin_bit_cast(int, p[r]) &
+                         __builtin_amdgcn_sbfe((int)word, 8 * (r >> 2) + (r & 3), 1));
+      }
+      Unit nnu;
+      bool nnext = false;
+      if (next) {
+        wait_loads();
+        load_k<T, D>(k, kst, s);
+        acc0 = M::dot(k, q);
+        nnext = it.next(nnu);
+        if (nnext) fetch_k<T, D>(kst, Kh, s, nnu, L);
+      }
+      check_v<T, D>(z, v0, u);
+      M::pv(o, v0, p, 0);
+      if (!kF32 || D != 64) load_v<T, D>(v1, Vh, s, u, 1, L);
+      check_v<T, D>(z, v1, u);
+      M::pv(o, v1, p, 1);
+      if (OUT) write_values(Ph, nnz, p, bits, u, unit_pos(rrs[s.qi], row_begin, u), s, vst);
+      if (OUT == 2)
+        write_columns(Pt + (size_t)blockIdx.x * nnz, nnz, p, s.row_valid ? bits : 0u, u, cols, s, L,
+                      vst);
+      u = nu, nu = nnu, more = next, next = nnext;
+    }
+    if constexpr (kF32) {
+      __syncthreads();
+      if (z != z) sh.redo = 1;
+      __syncthreads();
+      if (sh.redo) {   // from the P just written
+        __threadfence_block();
+        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
+          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
+          if (i >= 0)
+            spmm_row<D, OutT, false>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+        }
+        __syncthreads();
+        continue;
+      }
+    }
+    combine<D, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
+    __syncthreads();   // LDS is reused by the next slice
+  }
+}
+
 #ifdef SPLAT_DEBUG_BOUNDS
 // One index check on the device (the checked build's own test): out = the
 // checked index.
@@ -882,53 +1149,51 @@ inline dim3 slice_grid(const DevAcsr& a, int BH) {
   return dim3((unsigned)BH, (unsigned)(n < kMaxGridY ? n : kMaxGridY));
 }
 
-// Whether a launch is better off with a wavefront per row.  Times in us beyond
-// a launch's own 3.2, fitted to 39 launches (4 k to 6.2 M non-zeros over all
-// heads, every mask family, d = 64 and 128), which they meet within 35%:
-//   rows:   0.65 ns a row and 0.035 ns a non-zero (d = 64) at throughput; the
-//           longest row's keys one after the other, 52 ns each
-//   slices: 16 ns a slice and 2.5 ps a computed score at throughput; the
-//           longest slice's chain, 2.6 us per two tiles.
-// Measured, rows against slices: window 16, L = 256, one head 4.9 / 7.3;
-// strided+local 8 / 64, L = 512, one head 4.5 / 10.0; window 16, L = 1024, 4
-// heads 9.1 / 7.4; blocked 64, L = 512, 4 heads 15.1 / 7.2.
-bool rows_faster(const DevAcsr& a, int BH, int d) {
-  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
-  const double rows = fmax(0.65e-3 * R + 0.035e-3 * w * E, 0.052 * w * a.max_row_nnz);
-  const double slc =
-      fmax(16e-3 * kWavesPerGroup * a.n_groups * BH + 2.5e-6 * w * (double)a.computed * BH,
-           w * (1.6 + 2.6 * ((a.max_slice_tiles + 1) / 2)));
-  return rows < slc;
+// Estimated times, in us beyond a launch's own 2.5 to 3.2, by which a launch
+// chooses its kernel; fitted to 39 fp32 launches (4 k to 13 M non-zeros over
+// all heads, every mask family, d = 64 and 128).
+struct Size {
+  double w, R, E, C, NS;   // d / 64; rows, non-zeros, computed scores and slices of all heads
+  double longest, chain;   // the longest row's keys, the longest slice's tiles in pairs
+  Size(const DevAcsr& a, int BH, int d)
+      : w(d / 64.0), R((double)a.L * BH), E((double)a.nnz * BH), C((double)a.computed * BH),
+        NS((double)kWavesPerGroup * a.n_groups * BH), longest(a.max_row_nnz),
+        chain((a.max_slice_tiles + 1) / 2) {}
+};
+// At throughput a cost per slice and per computed score; else the longest slice.
+double slices_us(const Size& z, double per_slice, double per_score, double chain) {
+  return fmax(1e-3 * per_slice * z.NS + 1e-6 * per_score * z.w * z.C, chain);
 }
-
-// The same for R-SDDMM (fitted to the same launches), where a wavefront per row
-// pays only while the launch is bound by latency.  Measured, rows against
-// slices: window 16, L = 256, one head 2.8 / 6.1 us, L = 4096 6.9 / 6.3;
-// strided+local 8 / 64, L = 2048, one head 5.2 / 8.6, 12 heads 36 / 17.
-bool rsddmm_rows_faster(const DevAcsr& a, int BH, int d) {
-  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
-  if (R > 4096) return false;
-  const double rows =
-      fmax(0.5e-3 * R + 0.027e-3 * w * E, 0.9 * w * ((a.max_row_nnz + 63) / 64));
-  const double slc =
-      fmax(5.5e-3 * kWavesPerGroup * a.n_groups * BH + 2.2e-6 * w * (double)a.computed * BH,
-           (w + 1) / 2 * (2.2 + 2.4 * ((a.max_slice_tiles + 1) / 2)));
-  return rows < slc;
+// Fused, measured with a wavefront per row against slices: window 16, L = 256,
+// one head 4.9 / 7.3; strided+local 8 / 64, L = 512, one head 4.5 / 10.0;
+// window 16, L = 1024, 4 heads 9.1 / 7.4; blocked 64, L = 512, 4 heads 15.1 / 7.2.
+bool fused_rows_faster(const Size& z) {
+  return fmax(0.65e-3 * z.R + 0.035e-3 * z.w * z.E, 0.052 * z.w * z.longest) <
+         slices_us(z, 16, 2.5, z.w * (1.6 + 2.6 * z.chain));
 }
-
-// And for R-SpMM, where a wavefront per row reads V and P in whole lines and
-// pays over a wider range.  Measured, rows against slices: window 16, L = 256,
-// one head 3.1 / 6.1 us; strided+local 8 / 64, L = 2048, 12 heads 14.6 / 16.5;
-// strided+local 128, L = 2048, 12 heads 36.5 / 20.6; full, L = 128, d = 128, 4
-// heads 5.6 / 7.2.
-bool rspmm_rows_faster(const DevAcsr& a, int BH, int d) {
-  const double w = d / 64.0, R = (double)a.L * BH, E = (double)a.nnz * BH;
-  const double rows = fmax(0.25e-3 * R + 0.0085e-3 * w * E, 0.022 * w * a.max_row_nnz);
-  const double slc =
-      fmax(7.5e-3 * kWavesPerGroup * a.n_groups * BH + 2.2e-6 * w * (double)a.computed * BH,
-           (w + 1) / 2 * (2.2 + 2.4 * ((a.max_slice_tiles + 1) / 2)));
-  return rows < slc;
+// R-SDDMM, where a wavefront per row pays only while the launch is bound by
+// latency: window 16, L = 256, one head 2.6 / 6.1, L = 4096 6.9 / 6.3;
+// strided+local 8 / 64, L = 2048, one head 4.9 / 8.6, 12 heads 36 / 17.
+double rsddmm_rows_us(const Size& z) {
+  return fmax(0.5e-3 * z.R + 0.027e-3 * z.w * z.E, 0.9 * z.w * ceil(z.longest / 64));
 }
+double rsddmm_slices_us(const Size& z) {
+  return slices_us(z, 5.5, 2.2, (z.w + 1) / 2 * (2.2 + 2.4 * z.chain));
+}
+bool rsddmm_rows_faster(const Size& z) {
+  return z.R <= 4096 && rsddmm_rows_us(z) < rsddmm_slices_us(z);
+}
+// R-SpMM, where a wavefront per row reads V and P in whole lines and pays over
+// a wider range: window 16, L = 256, one head 3.0 / 6.1; strided+local 8 / 64,
+// L = 2048, 12 heads 14 / 16.5; strided+local 128, L = 2048, 12 heads 36.5 /
+// 20.6; full, L = 128, d = 128, 4 heads 5.6 / 7.2.
+double rspmm_rows_us(const Size& z) {
+  return fmax(0.25e-3 * z.R + 0.0085e-3 * z.w * z.E, 0.022 * z.w * z.longest);
+}
+double rspmm_slices_us(const Size& z) {
+  return slices_us(z, 7.5, 2.2, (z.w + 1) / 2 * (2.2 + 2.4 * z.chain));
+}
+bool rspmm_rows_faster(const Size& z) { return rspmm_rows_us(z) < rspmm_slices_us(z); }
 
 // Grid of the row kernels: four rows per workgroup.
 inline dim3 row_grid(const DevAcsr& a, int BH) {
@@ -947,7 +1212,7 @@ hipError_t fused_rows(const DevAcsr& a, int BH, const void* Q, const void* K, co
 template <typename T, int D>
 hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                    float scale, void* O, int out_dtype, hipStream_t st) {
-  if (rows_faster(a, BH, D))
+  if (fused_rows_faster(Size(a, BH, D)))
     return out_dtype == 0 ? fused_rows<D, float>(a, BH, Q, K, V, scale, O, st)
                           : fused_rows<D, __bf16>(a, BH, Q, K, V, scale, O, st);
   if (out_dtype == 0)
@@ -964,7 +1229,7 @@ hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const
 template <typename T, int D>
 hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, float scale, float* S,
                     hipStream_t st) {
-  if (rsddmm_rows_faster(a, BH, D)) {
+  if (rsddmm_rows_faster(Size(a, BH, D))) {
     hipLaunchKernelGGL((k_rsddmm_rows<D>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr, a.runs, a.L,
                        a.nnz, (const float*)Q, (const float*)K, scale, S);
     return hipGetLastError();
@@ -978,7 +1243,7 @@ hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, floa
 template <typename T, int D, typename OutT, bool COL>
 hipError_t rspmm_d(const DevAcsr& a, int BH, const float* P, const void* V, void* O,
                    hipStream_t st) {
-  if (rspmm_rows_faster(a, BH, D)) {
+  if (rspmm_rows_faster(Size(a, BH, D))) {
     hipLaunchKernelGGL((k_rspmm_rows<D, OutT, COL>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr,
                        a.runs, a.cols, a.L, a.nnz, P, (const float*)V, (OutT*)O);
     return hipGetLastError();
@@ -997,6 +1262,31 @@ hipError_t rspmm_t(const DevAcsr& a, int BH, int d, const float* P, const void* 
                           : rspmm_d<T, 64, __bf16, COL>(a, BH, P, V, O, st);
   return out_dtype == 0 ? rspmm_d<T, 128, float, COL>(a, BH, P, V, O, st)
                         : rspmm_d<T, 128, __bf16, COL>(a, BH, P, V, O, st);
+}
+
+template <typename T, int D, typename OutT>
+hipError_t chain_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
+                   float scale, float* P, float* Pt, void* O, hipStream_t st) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, slice_grid(a, BH), dim3(kThreads), 0, st, a.groups, a.rows,
+                       a.row_ptr, a.runs, a.tiles, a.masks, a.cols, a.L, a.nnz, slices(a),
+                       (const T*)Q, (const T*)K, (const T*)V, scale, P, Pt, (OutT*)O);
+    return hipGetLastError();
+  };
+  if (Pt) return go(k_chain_slices<T, D, OutT, 2>);
+  if constexpr (std::is_same<T, __bf16>::value)
+    if (!P) return go(k_chain_slices<T, D, OutT, 0>);
+  return go(k_chain_slices<T, D, OutT, 1>);
+}
+
+template <typename T>
+hipError_t chain_t(const DevAcsr& a, int BH, int d, const void* Q, const void* K, const void* V,
+                   float scale, float* P, float* Pt, void* O, int out_dtype, hipStream_t st) {
+  if (d == 64)
+    return out_dtype == 0 ? chain_d<T, 64, float>(a, BH, Q, K, V, scale, P, Pt, O, st)
+                          : chain_d<T, 64, __bf16>(a, BH, Q, K, V, scale, P, Pt, O, st);
+  return out_dtype == 0 ? chain_d<T, 128, float>(a, BH, Q, K, V, scale, P, Pt, O, st)
+                        : chain_d<T, 128, __bf16>(a, BH, Q, K, V, scale, P, Pt, O, st);
 }
 
 }  // namespace
@@ -1038,6 +1328,28 @@ hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, con
                             void* O, int out_dtype, bool colmajor, hipStream_t st) {
   return colmajor ? rspmm_t<float, true>(a, BH, d, P, V, O, out_dtype, st)
                   : rspmm_t<float, false>(a, BH, d, P, V, O, out_dtype, st);
+}
+
+// bf16, one kernel against the steps: blocked 64, L = 1024, 16 heads 9.9 /
+// 26.5 us, window 512 + 64 global, L = 4096, 64 heads 569 / 1006, window 4, L =
+// 4096, 64 heads 85 / 85; only where nearly all computed scores are outside a
+// mask of many slices do three launches pay (window 2: 85 / 82).  fp32: strided+
+// local 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
+bool chain_faster(const DevAcsr& a, int dtype, int BH, int d) {
+  const Size z(a, BH, d);
+  if (dtype != 0) return !(z.C > 16 * z.E && z.NS > 4096);
+  const double steps =
+      7.8 + 1.6e-6 * z.E +
+      (rsddmm_rows_faster(z) ? rsddmm_rows_us(z) : rsddmm_slices_us(z)) +
+      fmin(rspmm_rows_us(z), rspmm_slices_us(z));
+  return 3.2 + slices_us(z, 10, 4.2, (z.w + 1) / 2 * (1.2 + 5.6 * z.chain)) < steps;
+}
+
+hipError_t launch_chain(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
+                        const void* V, float scale, float* P, float* Pt, void* O, int out_dtype,
+                        hipStream_t st) {
+  return dtype == 0 ? chain_t<float>(a, BH, d, Q, K, V, scale, P, Pt, O, out_dtype, st)
+                    : chain_t<__bf16>(a, BH, d, Q, K, V, scale, P, Pt, O, out_dtype, st);
 }
 
 }  // namespace splat

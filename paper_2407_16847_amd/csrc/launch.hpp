@@ -45,6 +45,14 @@ hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, con
 hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, const void* V,
                             void* O, int out_dtype, bool colmajor, hipStream_t st);
 
+// The unfused chain in one kernel: P (row-major values), Pt (their
+// column-major copy, or null) and O.  P null: O alone (bf16 inputs only).
+// chain_faster: whether it beats the three or four launches of the steps.
+bool chain_faster(const DevAcsr& a, int dtype, int BH, int d);
+hipError_t launch_chain(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
+                        const void* V, float scale, float* P, float* Pt, void* O, int out_dtype,
+                        hipStream_t st);
+
 // Matrix-core kernels over the tile plan: bf16 inputs, d in {64, 128}.
 hipError_t launch_rsddmm_tiles(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                                float scale, float* S, hipStream_t st);

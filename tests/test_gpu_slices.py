@@ -111,3 +111,68 @@ def test_steps_f32(gpu_lib, kind, params, L, heads, d):
         x = Q[0, h].double() @ K[0, h].double().t() * scale
         mag = Q[0, h].double().abs() @ K[0, h].double().abs().t() * scale
         assert float(((S[0, h].cpu().double() - x[m]).abs() / mag[m]).max()) <= F32_REL
+
+
+# (dtype, alpha): the row-major and the column-major branch; windows of few
+# keys over many heads and short fp32 sequences take the chain of single steps,
+# the others one kernel
+CHAIN = [("full", {}, 33, 2), ("window", {"w": 5}, 65, 1), ("window", {"w": 2}, 4096, 40),
+         ("window", {"w": 150}, 321, 2), ("blocked", {"block": 33}, 300, 12),
+         ("dilated", {"w": 33, "dilation": 3}, 400, 12),
+         ("strided_local", {"local": 40, "stride": 33}, 500, 12),
+         ("strided_local", {"local": 4, "stride": 64}, 600, 2),
+         ("window_global", {"w": 3, "n_global": 1}, 4200, 1)]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind,params,L,heads", CHAIN)
+def test_chain(gpu_lib, kind, params, L, heads, dtype, d):
+    """O and the P left in S against the oracle; Pt is exactly P's column-major
+    copy; the allocation-free call gives the same O."""
+    splat = gpu_lib
+    print(f"[gpu] chain {kind} {params} L={L} heads={heads} d={d} {dtype}", flush=True)
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = _qkv(L, d, heads, L + 3 * d, dtype)
+    Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
+    M = om.dense_mask(kind, params, L)
+    n = min(heads, 2)
+    ref, _, Pref = oa.masked_attention(Q[:, :n], K[:, :n], V[:, :n], M, scale, want_csr=True)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L), columns=True)
+    col = a.info()["columns"] == 1
+    for alpha in (2.0, 0.0):
+        S = torch.full((1, heads, a.nnz), float("nan"), device="cuda")
+        Pt = torch.full_like(S, float("nan"))
+        O, used = splat.sparse_mhsa_unfused(a, Qd, Kd, Vd, scale, alpha=alpha, S=S, Pt=Pt,
+                                            out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        assert used == (col and alpha == 0.0)
+        if dtype == "f32":
+            assert _row_err(O[:, :n], ref) <= F32_REL
+        else:   # P enters the products with 16 bits, sums in fp32
+            assert float(np.abs(O[:, :n].cpu().numpy() - ref).max()) <= 1e-4
+        assert float(np.abs(S[:, :n].cpu().numpy() - Pref).max()) <= 1e-5
+        if used:
+            src = torch.from_numpy(om.colmajor_source(M))
+            assert torch.equal(Pt.cpu(), S.cpu()[:, :, src])
+        if heads * a.nnz * 8 + 256 <= splat.NOALLOC_SCRATCH_BYTES:
+            On, _ = splat.sparse_mhsa_unfused_noalloc(a, Qd, Kd, Vd, scale, alpha=alpha,
+                                                      out_dtype=torch.float32)
+            torch.cuda.synchronize()
+            assert torch.equal(On, O)
+
+
+def test_chain_without_keys(gpu_lib):
+    """An empty mask and empty rows: O = 0, nothing else is written."""
+    splat = gpu_lib
+    L, d = 70, 64
+    Q, K, V = (x.cuda() for x in _qkv(L, d, 2, 3))
+    for terms in ([], [dict(row_lo=40, lo_i=1, lo_c=-3, hi_i=1)]):
+        a = splat.Acsr(splat.Pattern.from_terms(L, terms))
+        for dt in (torch.float32, torch.bfloat16):
+            q, k, v = (x.to(dt) for x in (Q, K, V))
+            for O, _ in (splat.sparse_mhsa_unfused(a, q, k, v, 0.1),
+                         splat.sparse_mhsa_unfused_noalloc(a, q, k, v, 0.1)):
+                torch.cuda.synchronize()
+                assert (O[:, :, :40] == 0).all()
+                assert (O[:, :, 40:] == 0).all() if not terms else torch.isfinite(O).all()
