@@ -108,6 +108,11 @@ splat_status upload(splat_acsr* h) {
   h->dev.n_groups = (int32_t)a.groups.size();
   h->dev.computed = a.computed;
   h->dev.max_slice_tiles = 0;
+  h->dev.max_group_tiles = 0;
+  for (const splat::Group& g : a.groups)
+    h->dev.max_group_tiles = std::max(h->dev.max_group_tiles, g.tile_end - g.tile_begin);
+  h->dev.rows_aligned = a.nnz % 32 == 0;
+  for (int32_t p : a.row_ptr) h->dev.rows_aligned = h->dev.rows_aligned && p % 32 == 0;
   for (const splat::Group& g : a.groups)
     for (int w = 0; w < splat::kWavesPerGroup; ++w) {
       int32_t n = 0;
@@ -224,18 +229,13 @@ splat_status check_rspmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
 splat_status launch_rspmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
                           const float* P, const void* V, void* O, splat_dtype out_dtype,
                           bool colmajor, hipStream_t st) {
-  if (dtype == SPLAT_BF16)
-    return launched(splat::launch_rspmm_tiles(h->dev, B * H, d, P, V, O, out_dtype, colmajor, st),
-                    "rspmm");
-  return launched(
-      splat::launch_rspmm_f32(h->dev, B * H, d, P, V, O, out_dtype, colmajor, st), "rspmm");
+  return launched(splat::launch_rspmm(h->dev, dtype, B * H, d, P, V, O, out_dtype, colmajor, st),
+                  "rspmm");
 }
 
 splat_status launch_rsddmm(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
                            const void* Q, const void* K, float scale, float* S, hipStream_t st) {
-  if (dtype == SPLAT_BF16)
-    return launched(splat::launch_rsddmm_tiles(h->dev, B * H, d, Q, K, scale, S, st), "rsddmm");
-  return launched(splat::launch_rsddmm_f32(h->dev, B * H, d, Q, K, scale, S, st), "rsddmm");
+  return launched(splat::launch_rsddmm(h->dev, dtype, B * H, d, Q, K, scale, S, st), "rsddmm");
 }
 
 bool overlap(const float* a, const float* b, size_t n) {

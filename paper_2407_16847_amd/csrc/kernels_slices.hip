@@ -709,13 +709,15 @@ __device__ __forceinline__ void write_values(float* dst, int64_t nnz, const floa
   }
 }
 
-// The unit's values to their column-major places.  A register holds one key of
-// 32 rows, neighbours in the column: its store covers 128 bytes of it (of two,
-// one per half).  Lane i reads key i's descriptor; where every column steps by
-// one row, as in all but dilated masks, a value's place is (ptr - start) + row.
-__device__ __forceinline__ void write_columns(float* dst, int64_t nnz, const float (&x)[16],
-                                              uint32_t bits, const Unit& u, const ColRun* cols,
-                                              const Slice& s, int L, float* stage) {
+// f(r, place) for the keys of this lane that its row has: the value's place in
+// the head's column-major values.  Lane i reads key i's descriptor; where every
+// column steps by one row, as in all but dilated masks, a value's place is
+// (ptr - start) + row.  The column-wise analysis ends at 2^28 values a head, so
+// places times four fit 32 bits.
+template <typename F>
+__device__ __forceinline__ void for_each_place(uint32_t bits, int64_t nnz, const Unit& u,
+                                               const ColRun* cols, const Slice& s, int L,
+                                               float* stage, F&& f) {
   const ColRun mine = cols[s.key(u, s.qi, L)];
   const uint32_t b = bits >> (4 * s.h);
   if (__all(mine.stride == 1)) {
@@ -727,11 +729,8 @@ __device__ __forceinline__ void write_columns(float* dst, int64_t nnz, const flo
       const int4 c = *(const int4*)(base + 8 * g + 4 * s.h);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if ((b >> (8 * g + e)) & 1u) {
-          // the column-wise analysis ends at 2^28 values a head: 32-bit offsets
-          const int at = dbg::idx((&c.x)[e] + s.row, (int)nnz, dbg::kColPos);
-          *(float*)((char*)dst + 4u * (unsigned)at) = x[4 * g + e];
-        }
+        if ((b >> (8 * g + e)) & 1u)
+          f(4 * g + e, dbg::idx((&c.x)[e] + s.row, (int)nnz, dbg::kColPos));
     }
     wait_lds();
     return;
@@ -740,7 +739,7 @@ __device__ __forceinline__ void write_columns(float* dst, int64_t nnz, const flo
   for (int r = 0; r < 16; ++r) {
     const int k = 8 * (r >> 2) + (r & 3);
     const ColRun c = cols[s.key(u, k + 4 * s.h, L)];
-    if ((b >> k) & 1u) dst[dbg::idx((int64_t)col_pos(c, s.row), nnz, dbg::kColPos)] = x[r];
+    if ((b >> k) & 1u) f(r, dbg::idx(col_pos(c, s.row), (int)nnz, dbg::kColPos));
   }
 }
 
@@ -915,14 +914,11 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
       const uint32_t bits = s.row_valid ? s.bits(u) : 0u;
       float p[16];
       if (COL) {
-        const uint32_t b = bits >> (4 * s.h);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = s.key(u, 8 * (r >> 2) + 4 * s.h + (r & 3), L);
-          p[r] = (b >> (8 * (r >> 2) + (r & 3))) & 1u
-                     ? Ph[dbg::idx((int64_t)col_pos(cols[j], s.row), nnz, dbg::kColPos)]
-                     : 0.f;
-        }
+        for (int r = 0; r < 16; ++r) p[r] = 0.f;
+        for_each_place(bits, nnz, u, cols, s, L, sh.o[s.wave], [&](int r, int at) {
+          p[r] = *(const float*)((const char*)Ph + 4u * (unsigned)at);
+        });
       } else {
         const int pos = unit_pos(rr, row_begin, u);
         const float* src = Ph + pos;
@@ -1108,8 +1104,11 @@ __global__ __launch_bounds__(kThreads, D == 64 && sizeof(T) == 2 ? 3 : 2) void k
       M::pv(o, v1, p, 1);
       if (OUT) write_values(Ph, nnz, p, bits, u, unit_pos(rrs[s.qi], row_begin, u), s, vst);
       if (OUT == 2)
-        write_columns(Pt + (size_t)blockIdx.x * nnz, nnz, p, s.row_valid ? bits : 0u, u, cols, s, L,
-                      vst);
+        // a register holds one key of 32 rows, neighbours in the column: its store
+        // covers 128 bytes of it (of two, one per half)
+        for_each_place(s.row_valid ? bits : 0u, nnz, u, cols, s, L, vst, [&](int r, int at) {
+          *(float*)((char*)(Pt + (size_t)blockIdx.x * nnz) + 4u * (unsigned)at) = p[r];
+        });
       u = nu, nu = nnu, more = next, next = nnext;
     }
     if constexpr (kF32) {
@@ -1195,6 +1194,35 @@ double rspmm_slices_us(const Size& z) {
 }
 bool rspmm_rows_faster(const Size& z) { return rspmm_rows_us(z) < rspmm_slices_us(z); }
 
+// bf16 steps: slices against the 128-row kernels over tiles, which share each K
+// or V tile between four wavefronts and write S in whole 128-byte lines, but
+// walk a group's tiles one after the other.  Measured, tiles against slices:
+// R-SDDMM window 512 + 64 global, L = 4096, 16 heads 178 / 91 us, 64 heads 286 /
+// 349; blocked 64, L = 1024, 16 heads 9.4 / 5.9; window 4, d = 128, L = 1024, 16
+// heads 14.7 / 6.9, 64 heads 18.6 / 20.7.  Past the caches (192 MB; twice that
+// where rows begin and end on lines) the slices' partial lines cost: window 128,
+// L = 4096, 64 heads 102 / 130, full, L = 1024, 64 heads 98 / 70, L = 2048, 32
+// heads 145 / 168.
+bool rsddmm_bf16_slices(const DevAcsr& a, const Size& z) {
+  const double k = (z.w + 1) / 2;
+  const double value = z.E > (a.rows_aligned ? 96e6 : 48e6) ? 1.4e-6 : 0.75e-6;
+  const double slc =
+      2.5 + k * fmax(0.7 + 1.45 * z.chain, 5e-3 * z.NS + value * z.E);
+  const double tiles =
+      2.5 + fmax(3 + 2.75 * a.max_group_tiles, 3.5e-3 * z.NS + 1e-6 * k * z.E);
+  return slc < tiles;
+}
+// R-SpMM window 512 + 64 global, L = 4096, 16 heads 130 / 80 us, 64 heads 267 /
+// 318; blocked 64, L = 1024, 16 heads 7.7 / 5.9; full, L = 1024, 64 heads 48 / 71.
+bool rspmm_bf16_slices(const DevAcsr& a, const Size& z) {
+  const double k = (z.w + 1) / 2;
+  const double slc =
+      2.5 + fmax(0.9 + 1.5 * k * z.chain, k * (4.5e-3 * z.NS + 1.1e-6 * z.C));
+  const double tiles =
+      2 + fmax(4.5 + 2 * a.max_group_tiles, 3.5e-3 * z.NS + 0.75e-6 * k * z.C);
+  return slc < tiles;
+}
+
 // Grid of the row kernels: four rows per workgroup.
 inline dim3 row_grid(const DevAcsr& a, int BH) {
   return dim3((unsigned)BH, (unsigned)((a.L + 3) / 4));
@@ -1229,7 +1257,7 @@ hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const
 template <typename T, int D>
 hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, float scale, float* S,
                     hipStream_t st) {
-  if (rsddmm_rows_faster(Size(a, BH, D))) {
+  if (sizeof(T) == 4 && rsddmm_rows_faster(Size(a, BH, D))) {
     hipLaunchKernelGGL((k_rsddmm_rows<D>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr, a.runs, a.L,
                        a.nnz, (const float*)Q, (const float*)K, scale, S);
     return hipGetLastError();
@@ -1243,7 +1271,7 @@ hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, floa
 template <typename T, int D, typename OutT, bool COL>
 hipError_t rspmm_d(const DevAcsr& a, int BH, const float* P, const void* V, void* O,
                    hipStream_t st) {
-  if (rspmm_rows_faster(Size(a, BH, D))) {
+  if (sizeof(T) == 4 && rspmm_rows_faster(Size(a, BH, D))) {
     hipLaunchKernelGGL((k_rspmm_rows<D, OutT, COL>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr,
                        a.runs, a.cols, a.L, a.nnz, P, (const float*)V, (OutT*)O);
     return hipGetLastError();
@@ -1318,14 +1346,26 @@ hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, cons
                  : fused_d<float, 128>(a, BH, Q, K, V, scale, O, out_dtype, st);
 }
 
-hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
-                             float scale, float* S, hipStream_t st) {
+hipError_t launch_rsddmm(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
+                         float scale, float* S, hipStream_t st) {
+  if (dtype != 0) {
+    if (!rsddmm_bf16_slices(a, Size(a, BH, d)))
+      return launch_rsddmm_tiles(a, BH, d, Q, K, scale, S, st);
+    return d == 64 ? rsddmm_d<__bf16, 64>(a, BH, Q, K, scale, S, st)
+                   : rsddmm_d<__bf16, 128>(a, BH, Q, K, scale, S, st);
+  }
   return d == 64 ? rsddmm_d<float, 64>(a, BH, Q, K, scale, S, st)
                  : rsddmm_d<float, 128>(a, BH, Q, K, scale, S, st);
 }
 
-hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, const void* V,
-                            void* O, int out_dtype, bool colmajor, hipStream_t st) {
+hipError_t launch_rspmm(const DevAcsr& a, int dtype, int BH, int d, const float* P, const void* V,
+                        void* O, int out_dtype, bool colmajor, hipStream_t st) {
+  if (dtype != 0) {
+    if (!rspmm_bf16_slices(a, Size(a, BH, d)))
+      return launch_rspmm_tiles(a, BH, d, P, V, O, out_dtype, colmajor, st);
+    return colmajor ? rspmm_t<__bf16, true>(a, BH, d, P, V, O, out_dtype, st)
+                    : rspmm_t<__bf16, false>(a, BH, d, P, V, O, out_dtype, st);
+  }
   return colmajor ? rspmm_t<float, true>(a, BH, d, P, V, O, out_dtype, st)
                   : rspmm_t<float, false>(a, BH, d, P, V, O, out_dtype, st);
 }

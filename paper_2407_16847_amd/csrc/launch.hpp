@@ -16,6 +16,8 @@ struct DevAcsr {
   int32_t n_groups;
   int64_t computed;         // rows x keys of the non-empty wavefront tiles
   int32_t max_slice_tiles;  // non-empty tiles of the 32 rows that have the most
+  int32_t max_group_tiles;  // tiles of the row group that has the most
+  bool rows_aligned;        // every row's values begin on a 128-byte line of the head's
   const int32_t* row_ptr;   // L + 1
   const RowRuns* runs;      // L
   const int32_t* rows;      // L (grouped)
@@ -39,11 +41,12 @@ __device__ __forceinline__ int col_pos(const ColRun& c, int row) {
 // fp32: on the matrix cores, a workgroup per 32 rows, or a wavefront per row.
 hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st);
-hipError_t launch_rsddmm_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
-                             float scale, float* S, hipStream_t st);
+// The single steps, either dtype: the kernel that suits the launch.
 // colmajor: P holds the column-major values (requires a.cols).
-hipError_t launch_rspmm_f32(const DevAcsr& a, int BH, int d, const float* P, const void* V,
-                            void* O, int out_dtype, bool colmajor, hipStream_t st);
+hipError_t launch_rsddmm(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
+                         float scale, float* S, hipStream_t st);
+hipError_t launch_rspmm(const DevAcsr& a, int dtype, int BH, int d, const float* P, const void* V,
+                        void* O, int out_dtype, bool colmajor, hipStream_t st);
 
 // The unfused chain in one kernel: P (row-major values), Pt (their
 // column-major copy, or null) and O.  P null: O alone (bf16 inputs only).

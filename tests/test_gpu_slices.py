@@ -176,3 +176,35 @@ def test_chain_without_keys(gpu_lib):
                 torch.cuda.synchronize()
                 assert (O[:, :, :40] == 0).all()
                 assert (O[:, :, 40:] == 0).all() if not terms else torch.isfinite(O).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [2, 400])
+@pytest.mark.parametrize("kind,params,L", [c[:3] for c in CASES[:-1]])
+def test_steps_bf16(gpu_lib, kind, params, L, heads, d):
+    """Few heads take the slices, many the 128-row tile kernels."""
+    splat = gpu_lib
+    print(f"[gpu] steps bf16 {kind} {params} L={L} heads={heads} d={d}", flush=True)
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = _qkv(L, d, heads, L + 5 * d, "bf16")
+    M = om.dense_mask(kind, params, L)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L), columns=True)
+    S = torch.full((1, heads, a.nnz), float("nan"), device="cuda")
+    splat.rsddmm(a, Q.cuda(), K.cuda(), scale, S=S)
+    P = splat.row_softmax(a, S)
+    O = splat.rspmm(a, P, V.cuda(), out_dtype=torch.float32)
+    if a.info()["columns"] == 1:
+        Oc = splat.rspmm_colmajor(a, splat.transpose_colmajor(a, P), V.cuda(),
+                                  out_dtype=torch.float32)
+        assert torch.equal(Oc, O)
+    torch.cuda.synchronize()
+    assert torch.isfinite(S).all() and torch.isfinite(O).all()
+    m = torch.from_numpy(M)
+    for h in (0, heads - 1):
+        sel = slice(h, h + 1)
+        ref = oa.masked_attention(Q[:, sel], K[:, sel], V[:, sel], M, scale)
+        # P enters the products with 16 bits, sums in fp32
+        assert float(np.abs(O[:, sel].cpu().numpy() - ref).max()) <= 1e-4
+        q, k = Q[0, h].double(), K[0, h].double()
+        x, mag = q @ k.t() * scale, q.abs() @ k.abs().t() * scale
+        assert float(((S[0, h].cpu().double() - x[m]).abs() / mag[m]).max()) <= F32_REL
