@@ -208,3 +208,29 @@ def test_steps_bf16(gpu_lib, kind, params, L, heads, d):
         q, k = Q[0, h].double(), K[0, h].double()
         x, mag = q @ k.t() * scale, q.abs() @ k.abs().t() * scale
         assert float(((S[0, h].cpu().double() - x[m]).abs() / mag[m]).max()) <= F32_REL
+
+
+def test_binding_streams_and_outputs(gpu_lib):
+    """Calls go to the current stream; an output made by the call is plain and
+    contiguous whatever the class and the strides of size-1 axes of the input."""
+    splat = gpu_lib
+    L, d = 130, 64
+    Q, K, V = (x.cuda() for x in _qkv(L, d, 3, 9, "bf16"))
+    a = splat.Acsr(splat.Pattern.window(L, 20))
+    ref = splat.sparse_mhsa_fwd(a, Q, K, V, 0.1)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)        # the inputs change only after this
+        K2 = K * 0.5
+        O = splat.sparse_mhsa_fwd(a, Q, K2, V, 0.2)
+    side.synchronize()
+    # (0.5 K) at twice the scale: the same scores to bf16's rounding of Q * scale
+    assert float((O.float() - ref.float()).abs().max()) <= 2e-2
+    odd = Q.as_strided(Q.shape, (7, L * d, d, 1))     # the batch axis has size 1
+    assert odd.is_contiguous()
+    for q in (odd, torch.nn.Parameter(Q, requires_grad=False)):
+        O = splat.sparse_mhsa_fwd(a, q, K, V, 0.1)
+        torch.cuda.synchronize()
+        assert O.stride() == (3 * L * d, L * d, d, 1) and torch.equal(O, ref)
+        assert type(O) is torch.Tensor
