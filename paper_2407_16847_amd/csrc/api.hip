@@ -108,6 +108,7 @@ splat_status upload(splat_acsr* h) {
   h->dev.n_groups = (int32_t)a.groups.size();
   h->dev.computed = a.computed;
   h->dev.max_slice_tiles = 0;
+  h->dev.n_tiles = (int32_t)a.tiles.size();
   h->dev.max_group_tiles = 0;
   for (const splat::Group& g : a.groups)
     h->dev.max_group_tiles = std::max(h->dev.max_group_tiles, g.tile_end - g.tile_begin);

@@ -164,21 +164,28 @@ __device__ __forceinline__ void mask_scores(f32x16_t* s, uint64_t mk, int h) {
 // The plan arrays are kernel arguments of their own, const and __restrict__,
 // so their (wavefront-uniform) reads are scalar loads, independent of the
 // vector-memory counter that tracks the global->LDS loads.
-template <int D, typename OutT>
-__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void k_fused_mfma(
+//
+// NSET > 1: as many sets of four wavefronts share out a group's tiles, set s
+// taking tiles s, s + NSET, .. with a ring of its own; at the end set 0 takes
+// the others' O, sums and references over through LDS.  The references are
+// integers, so the factors between them are powers of two.
+template <int D, typename OutT, int NSET>
+__global__ __launch_bounds__(kThreads * NSET, D == 64 ? 4 : 2) void k_fused_mfma(
     const Group* __restrict__ groups, const int32_t* __restrict__ rows,
     const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks, int L, int BH,
     const __bf16* __restrict__ Q, const __bf16* K, const __bf16* V, float sl2,
     OutT* __restrict__ O) {
   using G = Geo<D>;
   constexpr int NKS = G::NKS, NDB = G::NDB, NSLOT = G::NSLOT, RB = G::RB;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];
 
   const int g = blockIdx.x / BH;
   const int bh = blockIdx.x - g * BH;
   const Group grp = groups[g];
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int set = NSET > 1 ? wave_all >> 2 : 0, wave = NSET > 1 ? wave_all & 3 : wave_all;
+  char* const smem = smem_all + set * G::LDS;
   const int qi = lane & 31, h = lane >> 5;
   const int m = wave * 32 + qi;
   const bool row_valid = m < grp.nrows;
@@ -231,22 +238,25 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void k_fused_mfma(
     // prologue: the first NSLOT-1 tiles
 #pragma unroll
     for (int sl = 0; sl < NSLOT - 1; ++sl)
-      issue_tile<D>(smem + sl * G::SLOT, tiles[tb + min(sl, nt - 1)], Kh, Vh, masks, L, wave,
-                    lane);
+      issue_tile<D>(smem + sl * G::SLOT, tiles[tb + min(sl * NSET + set, nt - 1)], Kh, Vh, masks, L,
+                    wave, lane);
     // descriptors are read one iteration before they are needed
-    Tile next_issue = tiles[tb + min(NSLOT - 1, nt - 1)];
-    int next_flags = tiles[tb].flags;
+    Tile next_issue = tiles[tb + min((NSLOT - 1) * NSET + set, nt - 1)];
+    int next_flags = tiles[tb + min(set, nt - 1)].flags;
     ring_sync<0>();
 
-    for (int i = 0; i < nt; ++i) {
+    const int ni = NSET > 1 ? (nt + NSET - 1) / NSET : nt;
+    for (int i = 0; i < ni; ++i) {
       char* cur = smem + (i % NSLOT) * G::SLOT;
       const Tile to_issue = next_issue;
       const int flags = next_flags;
-      next_issue = tiles[tb + min(i + NSLOT, nt - 1)];
-      next_flags = tiles[tb + min(i + 1, nt - 1)].flags;
+      next_issue = tiles[tb + min((i + NSLOT) * NSET + set, nt - 1)];
+      next_flags = tiles[tb + min((i + 1) * NSET + set, nt - 1)].flags;
       issue_tile<D>(smem + ((i + NSLOT - 1) % NSLOT) * G::SLOT, to_issue, Kh, Vh, masks, L, wave,
                     lane);
-      const int wst = (flags >> (kWaveShift + 2 * wave)) & 3;
+      const int wst = NSET > 1 && i * NSET + set >= nt
+                          ? kWaveEmpty
+                          : (flags >> (kWaveShift + 2 * wave)) & 3;
       if (wst != kWaveEmpty) {
         const __bf16* cK = (const __bf16*)cur;
         const __bf16* cV = (const __bf16*)(cur + G::TB);
@@ -336,6 +346,58 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void k_fused_mfma(
     }
   }
 
+  if constexpr (NSET > 1) {
+    // after the loop's last barrier no wavefront reads a ring: set 0 stages its
+    // output at the front (below), the other sets' states lie behind
+    constexpr int kState = NDB * 16 * 256;            // bytes of a wavefront's O
+    char* const states = smem_all + G::LDS;
+    float* const ml = (float*)(states + (NSET - 1) * 4 * kState);
+    static_assert(G::LDS + (NSET - 1) * 4 * (kState + 512) <= NSET * G::LDS, "states fit");
+    if (set > 0) {
+      char* const mine = states + ((set - 1) * 4 + wave) * kState;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *(float4*)(mine + (b * 4 + r) * 1024 + lane * 16) =
+              make_float4(oacc[b][4 * r], oacc[b][4 * r + 1], oacc[b][4 * r + 2],
+                          oacc[b][4 * r + 3]);
+      float* const st = ml + ((set - 1) * 4 + wave) * 128;
+      st[lane] = acc ? m_run : -INFINITY;
+      st[64 + lane] = l_run;
+    }
+    __syncthreads();
+    if (set > 0) return;
+    float mt = acc ? m_run : -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NSET - 1; ++q) mt = fmaxf(mt, ml[(q * 4 + wave) * 128 + lane]);
+    // a set without weight has 0 (or NaN) to add
+    auto factor = [&](float mq) { return mq == -INFINITY ? 0.f : exp2_hw(mq - mt); };
+    const float f0 = factor(acc ? m_run : -INFINITY);
+    l_run *= f0;
+#pragma unroll
+    for (int b = 0; b < NDB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[b][r] *= f0;
+#pragma unroll
+    for (int q = 0; q < NSET - 1; ++q) {
+      const float* const st = ml + (q * 4 + wave) * 128;
+      const float f = factor(st[lane]);
+      l_run = fmaf(st[64 + lane], f, l_run);
+      const char* const other = states + (q * 4 + wave) * kState;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float4 v = *(const float4*)(other + (b * 4 + r) * 1024 + lane * 16);
+          oacc[b][4 * r] = fmaf(v.x, f, oacc[b][4 * r]);
+          oacc[b][4 * r + 1] = fmaf(v.y, f, oacc[b][4 * r + 1]);
+          oacc[b][4 * r + 2] = fmaf(v.z, f, oacc[b][4 * r + 2]);
+          oacc[b][4 * r + 3] = fmaf(v.w, f, oacc[b][4 * r + 3]);
+        }
+    }
+  }
+
   const float l_tot = l_run + lane_xor32(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   // O leaves through LDS: each wavefront stages its 32 rows (rows padded by
@@ -368,27 +430,51 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void k_fused_mfma(
   }
 }
 
-template <int D, typename OutT>
+// How many sets of wavefronts share out a group's tiles: one, unless the longest
+// group walked tile by tile (0.84 us each at d = 64, 1.57 at 128) outlasts the
+// launch's tiles at throughput (2.5 and 5.7 ns each).  Measured, 1 / 2 / 4 sets:
+// full, L = 777, d = 128, 16 heads 24.2 / 19.9 us; full, L = 2048, d = 128, 16
+// heads 54 / 44; window 512 + 64 global, L = 4096, 16 heads 58 / 47 / 41, 32
+// heads 72 / 60 / 75, 64 heads 95 / 107; strided+local 128, L = 2048, 24 heads
+// (5 tiles) 11.3 / 12.5; full, L = 512, 8 heads 10.2 / 9.2 / 9.9.  Two sets
+// of d = 128 and four of d = 64 fill a CU's LDS and wavefronts.
+inline int fused_sets(const DevAcsr& a, int BH, int d) {
+  const double chain = (d == 64 ? 0.84 : 1.57) * a.max_group_tiles;
+  const double all = (d == 64 ? 2.5e-3 : 5.7e-3) * a.n_tiles * BH;
+  if (a.max_group_tiles < 8 || chain <= all) return 1;
+  return d == 64 && a.max_group_tiles >= 16 && chain / 2 > all ? 4 : 2;
+}
+
+template <int D, typename OutT, int NSET>
 hipError_t allow_lds() {
-  return hipFuncSetAttribute((const void*)k_fused_mfma<D, OutT>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, Geo<D>::LDS);
+  return hipFuncSetAttribute((const void*)k_fused_mfma<D, OutT, NSET>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, NSET * Geo<D>::LDS);
+}
+
+template <int D, typename OutT, int NSET>
+hipError_t fused_launch(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
+                        float sl2, void* O, hipStream_t st) {
+  hipLaunchKernelGGL((k_fused_mfma<D, OutT, NSET>), dim3(a.n_groups * BH), dim3(kThreads * NSET),
+                     NSET * Geo<D>::LDS, st, a.groups, a.rows, a.tiles, a.masks, a.L, BH,
+                     (const __bf16*)Q, (const __bf16*)K, (const __bf16*)V, sl2, (OutT*)O);
+  return hipGetLastError();
 }
 
 template <int D, typename OutT>
-hipError_t fused_launch(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
-                        float sl2, void* O, hipStream_t st) {
-  constexpr int lds = Geo<D>::LDS;
-  hipLaunchKernelGGL((k_fused_mfma<D, OutT>), dim3(a.n_groups * BH), dim3(kThreads), lds, st,
-                     a.groups, a.rows, a.tiles, a.masks, a.L, BH, (const __bf16*)Q,
-                     (const __bf16*)K, (const __bf16*)V, sl2, (OutT*)O);
-  return hipGetLastError();
+hipError_t fused_out(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
+                     float sl2, void* O, hipStream_t st) {
+  const int sets = fused_sets(a, BH, D);
+  if constexpr (D == 64)
+    if (sets == 4) return fused_launch<D, OutT, 4>(a, BH, Q, K, V, sl2, O, st);
+  return sets >= 2 ? fused_launch<D, OutT, 2>(a, BH, Q, K, V, sl2, O, st)
+                   : fused_launch<D, OutT, 1>(a, BH, Q, K, V, sl2, O, st);
 }
 
 template <int D>
 hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                    float sl2, void* O, int out_dtype, hipStream_t st) {
-  return out_dtype == 0 ? fused_launch<D, float>(a, BH, Q, K, V, sl2, O, st)
-                        : fused_launch<D, __bf16>(a, BH, Q, K, V, sl2, O, st);
+  return out_dtype == 0 ? fused_out<D, float>(a, BH, Q, K, V, sl2, O, st)
+                        : fused_out<D, __bf16>(a, BH, Q, K, V, sl2, O, st);
 }
 
 }  // namespace
@@ -396,10 +482,13 @@ hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const
 hipError_t bounds_collect_mfma(uint32_t* bits, bool clear) { return dbg::collect(bits, clear); }
 
 hipError_t prepare_fused_mfma() {
-  hipError_t e = allow_lds<64, float>();
-  if (e == hipSuccess) e = allow_lds<64, __bf16>();
-  if (e == hipSuccess) e = allow_lds<128, float>();
-  if (e == hipSuccess) e = allow_lds<128, __bf16>();
+  hipError_t e = hipSuccess;
+  auto also = [&](hipError_t x) { e = e == hipSuccess ? x : e; };
+  also(allow_lds<64, float, 1>()), also(allow_lds<64, __bf16, 1>());
+  also(allow_lds<64, float, 2>()), also(allow_lds<64, __bf16, 2>());
+  also(allow_lds<64, float, 4>()), also(allow_lds<64, __bf16, 4>());
+  also(allow_lds<128, float, 1>()), also(allow_lds<128, __bf16, 1>());
+  also(allow_lds<128, float, 2>()), also(allow_lds<128, __bf16, 2>());
   return e;
 }
 

@@ -16,6 +16,7 @@ struct DevAcsr {
   int32_t n_groups;
   int64_t computed;         // rows x keys of the non-empty wavefront tiles
   int32_t max_slice_tiles;  // non-empty tiles of the 32 rows that have the most
+  int32_t n_tiles;
   int32_t max_group_tiles;  // tiles of the row group that has the most
   bool rows_aligned;        // every row's values begin on a 128-byte line of the head's
   const int32_t* row_ptr;   // L + 1

@@ -234,3 +234,32 @@ def test_binding_streams_and_outputs(gpu_lib):
         torch.cuda.synchronize()
         assert O.stride() == (3 * L * d, L * d, d, 1) and torch.equal(O, ref)
         assert type(O) is torch.Tensor
+
+
+# groups of 7 (one set of wavefronts), 9, 13 (two), 17 and 23 tiles (four at d =
+# 64), a last group of few rows, empty tiles; scores around 0, and rising with
+# the key so that the sets end with references far apart
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rise", [0.0, 12.0])
+@pytest.mark.parametrize("kind,params,L", [
+    ("full", {}, 448), ("full", {}, 520), ("full", {}, 777), ("full", {}, 1088),
+    ("window", {"w": 500}, 1450), ("window_global", {"w": 30, "n_global": 3}, 1300),
+    ("strided_local", {"local": 600, "stride": 100}, 900)])
+def test_fused_sets(gpu_lib, kind, params, L, rise, d):
+    splat = gpu_lib
+    print(f"[gpu] fused sets {kind} {params} L={L} rise={rise} d={d}", flush=True)
+    scale = 1.0 / math.sqrt(d)
+    Q, K, V = _qkv(L, d, 3, L + d, "f32")
+    if rise:   # q and k along one direction u, |u|^2 * scale = 8
+        u = math.sqrt(8.0 / (scale * d))
+        c = torch.arange(L).float()[:, None] / L
+        Q, K = 2.0 * u + 0.05 * Q, rise * c * u + 0.3 * K
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    M = om.dense_mask(kind, params, L)
+    ref = oa.masked_attention(Q, K, V, M, scale)
+    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale, out_dtype=torch.float32)
+    Ob = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+    torch.cuda.synchronize()
+    assert float(np.abs(O.cpu().numpy() - ref).max()) <= 2e-2
+    assert float(np.abs(Ob.float().cpu().numpy() - ref).max()) <= 2e-2
