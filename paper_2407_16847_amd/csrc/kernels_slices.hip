@@ -228,6 +228,14 @@ struct Slice {
   }
 };
 
+// waits for this wavefront's LDS reads, and for its loads from memory
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+
 // A unit's K rows go from memory into the wavefront's own LDS, 1 KB of whole
 // rows per load, and from there into the operand: loaded straight into the
 // operand, each load would touch 32 rows, 32 bytes of each, and K would hold
@@ -241,6 +249,7 @@ template <typename T, int D>
 __device__ __forceinline__ void fetch_k(float* stage, const char* Kh, const Slice& s, const Unit& u,
                                         int L) {
   constexpr int RB = D * (int)sizeof(T), CPR = RB / 16, RPL = 64 / CPR;
+  wait_lds();   // the unit before it has left the LDS rows that these loads fill
 #pragma unroll
   for (int k = 0; k < kUnit / RPL; ++k) {
     const int r = RPL * k + s.lane / CPR;
@@ -258,14 +267,6 @@ __device__ __forceinline__ void load_k(typename Mat<T, D>::Row& x, const float* 
     x.v[t] = *(const typename std::remove_reference<decltype(x.v[0])>::type*)((const char*)stage +
                                                                              (off ^ (32 * t)));
 }
-// waits for this wavefront's LDS reads, and for its loads from memory
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void wait_loads() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-  asm volatile("" ::: "memory");
-}
-
 template <typename T, int D>
 __device__ __forceinline__ void load_v(typename Mat<T, D>::V& x, const char* Vh, const Slice& s,
                                        const Unit& u, int j, int L) {
