@@ -264,6 +264,11 @@ bool use_colmajor(const HostAcsr& a, float alpha) {
   return a.col_regular == 1 && a.nnz > 0 && density >= (double)alpha;
 }
 
+// Do the byte ranges [a, a + na) and [b, b + nb) meet?
+bool meet(const void* a, size_t na, const void* b, size_t nb) {
+  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // The unfused chain.  keep_values: the caller reads P in S (and Pt) afterwards;
 // without it a bf16 chain that runs as one kernel leaves them alone.
 splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
@@ -281,7 +286,14 @@ splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
   CHECK(check_ptr(K, "K"));
   CHECK(check_rspmm(h, dtype, B, H, d, S, V, O, out_dtype, false));
   if (col) CHECK(check_transpose(h, B, H, S, Pt));
-  if (splat::chain_faster(h->dev, dtype, B * H, d)) {
+  // The steps are done with Q and K before they write Pt and O, so these may
+  // share memory with them; one kernel's workgroups are not done together.
+  const size_t elems = (size_t)B * H * a.L * d, in = elems * (dtype == SPLAT_BF16 ? 2 : 4);
+  const size_t out = elems * (out_dtype == SPLAT_BF16 ? 2 : 4);
+  const size_t vals = (size_t)B * H * a.nnz * 4;
+  const bool shared = meet(O, out, Q, in) || meet(O, out, K, in) ||
+                      (col && (meet(Pt, vals, Q, in) || meet(Pt, vals, K, in)));
+  if (!shared && splat::chain_faster(h->dev, dtype, B * H, d)) {
     const bool values = keep_values || dtype != SPLAT_BF16;
     if (used_colmajor) *used_colmajor = col ? 1 : 0;
     return launched(splat::launch_chain(h->dev, dtype, B * H, d, Q, K, V, scale,

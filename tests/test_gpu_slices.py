@@ -162,6 +162,26 @@ def test_chain(gpu_lib, kind, params, L, heads, dtype, d):
             assert torch.equal(On, O)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("onto", ["Q", "K"])
+def test_chain_output_over_an_input(gpu_lib, onto, noalloc, dtype):
+    """O may take the place of Q or K (the steps are done with both before O
+    is written): the same result as in a tensor of its own."""
+    splat = gpu_lib
+    L, d, heads = 1000, 64, 16
+    q, k, v = (x.cuda() for x in _qkv(L, d, heads, 21, dtype))
+    a = splat.Acsr(splat.Pattern.window(L, 100))
+    call = splat.sparse_mhsa_unfused_noalloc if noalloc else splat.sparse_mhsa_unfused
+    ref = call(a, q, k, v, 0.125)[0]
+    O = call(a, q, k, v, 0.125, O=q if onto == "Q" else k)[0]
+    torch.cuda.synchronize()
+    # two orders of the same sums: fp32 rounding, for bf16 one step of O's
+    tol = 2.0 ** -8 if dtype == "bf16" else F32_REL
+    err = (O.double() - ref.double()).abs().amax(-1) / ref.double().abs().amax(-1)
+    assert float(err.max()) <= 2 * tol
+
+
 def test_chain_without_keys(gpu_lib):
     """An empty mask and empty rows: O = 0, nothing else is written."""
     splat = gpu_lib
