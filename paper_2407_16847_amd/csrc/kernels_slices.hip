@@ -827,7 +827,9 @@ __global__ __launch_bounds__(64) void k_rsddmm_rows(
 // COL: P holds the head's values in column-major order, value (i, j) at
 // col_pos(cols[j], i).  fp32, a wavefront per row against slices: strided+local
 // 128, L = 2048, 12 heads 54 -> 20.6 us; dilated 3, L = 1000, d = 128, 8 heads
-// 64 -> 20.6; per unit 32 MFMAs (d = 64) and V's 8 KB against P's 4 KB.
+// 64 -> 20.6, and with the walk advanced after V's loads, which ended the
+// spills, 22.1 -> 19.1 under a kernel trace; per unit 32 MFMAs (d = 64) and V's
+// 8 KB against P's 4 KB.
 
 // O of row i by one wavefront, lanes over the features.
 template <int D, typename OutT, bool COL>
