@@ -352,6 +352,27 @@ __device__ __forceinline__ void check_v(float& z, const typename Mat<T, D>::V& v
   }
 }
 
+// Sums near the end of fp32's range.  The fused kernel's weights reach
+// 2^kRefSlack before the division by their sum, where a row's own keys one
+// after the other, each against the largest score so far, keep them at 1 and
+// below: O can pass the largest float here and not there.  A wavefront whose
+// partial O holds 2^125 or more (four sums below that stay below 2^127) has
+// the slice redone row by row.  It would find what check_v finds as well, but
+// the loop without check_v is scheduled worse (window 256 + 32 global, L = 2048,
+// 12 heads 59 -> 73 us).
+template <int NB>
+__device__ __forceinline__ bool near_end(const f32x16_t (&o)[NB]) {
+  unsigned top = 0;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = o[b][r];   // (a bit cast of a vector's element takes element 0)
+      top = max(top, __builtin_bit_cast(unsigned, x) & 0x7fffffffu);
+    }
+  return top >= 0x7e000000u;
+}
+
 // --------------------------------------------------------- combining, output
 // LDS of a slice kernel: each wavefront's partial O (its staging area before
 // that), the row references and sums.
@@ -627,7 +648,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     __syncthreads();
     if (s.h == 0) sh.m[s.wave][s.qi] = m, sh.l[s.wave][s.qi] = l;
     if constexpr (std::is_same<T, float>::value) {
-      if (z != z) sh.redo = 1;
+      if (z != z || near_end<NB>(o)) sh.redo = 1;
       __syncthreads();
       if (sh.redo) {
         for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {

@@ -92,6 +92,28 @@ def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, wh
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("big", [1e37, 2e36])
+def test_fused_f32_large_values(gpu_lib, big, d):
+    """V near fp32's end: keys that score 7 binary orders above a wavefront's
+    first unit, one in the second unit of each wavefront, outgrow fp32 before
+    the division by the sum (big = 2e36: only over all four), the result does
+    not."""
+    splat = gpu_lib
+    L, heads, scale = 300, 12, 1.0 / math.sqrt(d)
+    print(f"[gpu] fused f32 V up to {big} d={d}", flush=True)
+    _, K, V = _qkv(L, d, heads, 31)
+    Q, K = torch.ones_like(K), 1e-3 * K
+    for j in (130, 170, 200, 230):
+        K[:, :, j] += 7.0 * math.log(2.0) / (scale * d)
+        V[:, :, j] *= big / V[:, :, j].abs().amax(-1, keepdim=True)
+    a = splat.Acsr(splat.Pattern.full(L))
+    ref = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], om.dense_mask("full", {}, L), scale)
+    O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+    torch.cuda.synchronize()
+    assert _row_err(O[:, :2], ref) <= F32_REL
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("kind,params,L,heads", CASES)
 def test_steps_f32(gpu_lib, kind, params, L, heads, d):
     splat = gpu_lib
