@@ -469,7 +469,10 @@ __device__ __forceinline__ void fused_row(int i, int lane, const RowRuns* runs,
   const RowRuns rr = runs[i];
   const int n = row_ptr[i + 1] - row_ptr[i];
   const float* const q = Qh + (size_t)i * D;
-  float m = -INFINITY, l = 0.f, acc[NC];
+  // m: the largest score so far, from the lowest float on: against that a score
+  // of -inf weighs 0 (against -inf itself NaN).  O of a row without keys is 0 / 1,
+  // of one whose keys all score -inf 0 / 0.
+  float m = -__FLT_MAX__, l = n > 0 ? 0.f : 1.f, acc[NC];
 #pragma unroll
   for (int b = 0; b < NC; ++b) acc[b] = 0.f;
 #pragma unroll 1
@@ -490,7 +493,7 @@ __device__ __forceinline__ void fused_row(int i, int lane, const RowRuns* runs,
       x = ((d[0] + d[1]) + (d[2] + d[3])) * scale;
     }
     const float mn = fmaxf(m, wave_max(x));
-    const float alpha = expf(m - mn);            // 0 on the first step (m = -inf)
+    const float alpha = expf(m - mn);
     const float p = valid ? expf(x - mn) : 0.f;
     l = l * alpha + wave_sum(p);
 #pragma unroll
@@ -512,7 +515,7 @@ __device__ __forceinline__ void fused_row(int i, int lane, const RowRuns* runs,
     for (; t < cnt; ++t) key(t);
     m = mn;
   }
-  const float inv = l > 0.f ? 1.f / l : 0.f;
+  const float inv = 1.f / l;
 #pragma unroll
   for (int b = 0; b < NC; ++b) store1(Oh + (size_t)i * D + 64 * b + lane, acc[b] * inv);
 }

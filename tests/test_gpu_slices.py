@@ -91,6 +91,35 @@ def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, wh
             assert torch.isfinite(O[:, :, ~clean, 4:]).all(), name
 
 
+# a wavefront per row (68 keys of one head), slices, and slices redone row by
+# row: V of key 199, which the compared rows lack, is infinite
+@pytest.mark.parametrize("kind,params,L,heads,rows,redo", [
+    ("full", {}, 68, 1, 68, False), ("full", {}, 68, 64, 68, False),
+    ("window", {"w": 100}, 200, 4, 99, False), ("window", {"w": 100}, 200, 4, 99, True)])
+def test_fused_f32_first_scores_minus_infinity(gpu_lib, kind, params, L, heads, rows, redo):
+    """Rows whose first 64 keys score -inf return the softmax over the others;
+    rows whose keys all do return NaN."""
+    splat = gpu_lib
+    d, scale = 64, 0.125
+    print(f"[gpu] fused f32 -inf scores {kind} {params} L={L} heads={heads} redo={redo}", flush=True)
+    Q, K, V = _qkv(L, d, heads, 41)
+    M = om.dense_mask(kind, params, L)
+    seen = M.copy()
+    seen[:, :64] = False
+    Q[..., 0] = K[..., 0] = 0.0
+    ref = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], seen, scale)
+    Q[..., 0], K[:, :, :64, 0] = 1.0, -math.inf
+    if redo:
+        V[:, :, 199] = math.inf
+    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+    K[..., 0] = -math.inf
+    none = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+    torch.cuda.synchronize()
+    assert _row_err(O[:, :2, :rows], ref[:, :, :rows]) <= F32_REL
+    assert torch.isnan(none).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("big", [1e37, 2e36])
 def test_fused_f32_large_values(gpu_lib, big, d):
