@@ -338,8 +338,9 @@ __device__ __forceinline__ void mask_unit(float (&t)[16], uint32_t bits, int h) 
 // The matrix cores multiply every key row by every query's weight, 0 for the
 // queries that do not have the key, and 0 * inf is NaN.  z turns NaN when V
 // holds an infinity or a NaN in half a unit in which some row lacks some key;
-// the slice is then redone row by row (the *_row functions below).  With bf16
-// V no such check is made: there a row may see the keys of its tile.
+// the slice's rows are then formed again row by row (the *_row functions
+// below).  With bf16 V no such check is made: there a row may see the keys of
+// its tile.
 template <typename T, int D>
 __device__ __forceinline__ void check_v(float& z, const typename Mat<T, D>::V& v, const Unit& u) {
   if constexpr (std::is_same<T, float>::value) {
@@ -352,27 +353,6 @@ __device__ __forceinline__ void check_v(float& z, const typename Mat<T, D>::V& v
   }
 }
 
-// Sums near the end of fp32's range.  The fused kernel's weights reach
-// 2^kRefSlack before the division by their sum, where a row's own keys one
-// after the other, each against the largest score so far, keep them at 1 and
-// below: O can pass the largest float here and not there.  A wavefront whose
-// partial O holds 2^125 or more (four sums below that stay below 2^127) has
-// the slice redone row by row.  It would find what check_v finds as well, but
-// the loop without check_v is scheduled worse (window 256 + 32 global, L = 2048,
-// 12 heads 59 -> 73 us).
-template <int NB>
-__device__ __forceinline__ bool near_end(const f32x16_t (&o)[NB]) {
-  unsigned top = 0;
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float x = o[b][r];   // (a bit cast of a vector's element takes element 0)
-      top = max(top, __builtin_bit_cast(unsigned, x) & 0x7fffffffu);
-    }
-  return top >= 0x7e000000u;
-}
-
 // --------------------------------------------------------- combining, output
 // LDS of a slice kernel: each wavefront's partial O (its staging area before
 // that), the row references and sums.
@@ -382,7 +362,7 @@ struct Shared {
   float o[kWavesPerGroup][kWaveRows * OS];
   float m[kWavesPerGroup][kWaveRows];
   float l[kWavesPerGroup][kWaveRows];
-  int redo;                                        // some V value is not finite
+  unsigned redo;                                   // rows to be formed again row by row
 };
 
 template <typename OutT>
@@ -392,7 +372,14 @@ __device__ __forceinline__ void store_o4(OutT* p, f32x4_t v) {
 
 // Sum of the wavefronts' O^T, times inv(row i), written as whole rows: every
 // thread sums four features of one row at a time, eight lanes along a row.
-template <int D, typename OutT, typename F>
+// CHECK: a row whose result is not finite is marked in sh.redo instead, for the
+// caller to form the marked rows again one by one.  That order of the sums may
+// stay within fp32's range where this one does not, and the row code keeps the
+// fused kernel's weights at 1 and below, which reach 2^kRefSlack before the
+// division by their sum here.  (It would find what check_v finds too, but
+// without check_v the fused loop is scheduled worse: window 256 + 32 global, L =
+// 2048, 12 heads 59 -> 73 us.)
+template <int D, bool CHECK, typename OutT, typename F>
 __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 32], const Slice& s,
                                         OutT* Oh, F&& inv) {
   constexpr int NB = D / 32, OS = Shared<D>::OS;
@@ -412,14 +399,34 @@ __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 3
   if (lane_r >= 0) {
     const float f = inv(r, lane_r);
     OutT* const orow = Oh + (size_t)lane_r * D;
+    f32x4_t v[NB];
+    float z = 0.f;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int c = 4 * (threadIdx.x & 7) + 32 * k;
-      f32x4_t v = *(const f32x4_t*)(sh.o[0] + r * OS + c);
+      v[k] = *(const f32x4_t*)(sh.o[0] + r * OS + c);
 #pragma unroll
-      for (int w = 1; w < kWavesPerGroup; ++w) v += *(const f32x4_t*)(sh.o[w] + r * OS + c);
-      store_o4<OutT>(orow + c, v * f);
+      for (int w = 1; w < kWavesPerGroup; ++w) v[k] += *(const f32x4_t*)(sh.o[w] + r * OS + c);
+      v[k] *= f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z = fmaf(v[k][e], 0.f, z);
     }
+    // nothing of such a row, or of one marked before, is stored: O may lie over Q
+    if (CHECK) {
+      if ((__ballot(z != z) >> (s.lane & 56)) & 0xffu) atomicOr(&sh.redo, 1u << r);
+      if ((sh.redo >> r) & 1u) return;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) store_o4<OutT>(orow + 4 * (threadIdx.x & 7) + 32 * k, v[k]);
+  }
+}
+
+// f(row) by the wavefronts in turn, for the rows of the slice set in `rows`
+template <typename F>
+__device__ __forceinline__ void for_rows(unsigned rows, const Slice& s, F&& f) {
+  for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
+    const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
+    if (i >= 0 && ((rows >> r) & 1u)) f(i);
   }
 }
 
@@ -650,22 +657,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     l += lane_xor32(l);
     __syncthreads();
     if (s.h == 0) sh.m[s.wave][s.qi] = m, sh.l[s.wave][s.qi] = l;
-    if constexpr (std::is_same<T, float>::value) {
-      if (z != z || near_end<NB>(o)) sh.redo = 1;
-      __syncthreads();
-      if (sh.redo) {
-        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
-          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
-          if (i >= 0)
-            fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
-                               O + head);
-        }
-        __syncthreads();
-        continue;
-      }
-    } else {
-      __syncthreads();
-    }
+    if (z != z) sh.redo = ~0u;
+    __syncthreads();
     // row i's reference over the wavefronts, and a wavefront's factor to it
     auto top = [&](int i) {
       return fmaxf(fmaxf(sh.m[0][i], sh.m[1][i]), fmaxf(sh.m[2][i], sh.m[3][i]));
@@ -676,7 +669,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[b][r] *= f;
-    combine<D, OutT>(sh, o, s, O + head, [&](int i, int row) {
+    combine<D, std::is_same<T, float>::value, OutT>(sh, o, s, O + head, [&](int i, int row) {
       const float mt = top(i);
       float lt = 0.f;
 #pragma unroll
@@ -686,6 +679,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
       return lt == 0.f && row_ptr[row] != row_ptr[row + 1] ? NAN : 0.f;
     });
     __syncthreads();   // LDS is reused by the next slice
+    if constexpr (std::is_same<T, float>::value)
+      if (sh.redo) {
+        for_rows(sh.redo, s, [&](int i) {
+          fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
+                             O + head);
+        });
+        __syncthreads();
+      }
   }
 }
 
@@ -917,7 +918,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
   // steps, window 512 + 64 global, 16 heads 273.0 -> 271.7 us).  fp32 is bound by
   // its products and d = 128 by registers: ahead 45.8 us against 44.7 (three
   // steps, dilated 3, L = 1000, d = 128, 8 heads).
-  constexpr bool kAhead = sizeof(T) == 2;
+  constexpr bool kAhead = sizeof(T) == 2, kF32 = !kAhead;
   constexpr int NB = D / 32;
   __shared__ __attribute__((aligned(16))) Shared<D> sh;
   const size_t head = (size_t)blockIdx.x * L * D;
@@ -986,22 +987,19 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
         for (int r = 0; r < 16; ++r) p[r] = pn[r];
       u = nu, more = next;
     }
-    if constexpr (std::is_same<T, float>::value) {
+    if constexpr (kF32) {
       __syncthreads();
-      if (z != z) sh.redo = 1;
-      __syncthreads();
-      if (sh.redo) {
-        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
-          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
-          if (i >= 0)
-            spmm_row<D, OutT, COL>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
-        }
-        __syncthreads();
-        continue;
-      }
+      if (z != z) sh.redo = ~0u;
     }
-    combine<D, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
+    combine<D, kF32, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
     __syncthreads();   // LDS is reused by the next slice
+    if constexpr (kF32)
+      if (sh.redo) {
+        for_rows(sh.redo, s, [&](int i) {
+          spmm_row<D, OutT, COL>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+        });
+        __syncthreads();
+      }
   }
 }
 
@@ -1158,21 +1156,18 @@ __global__ __launch_bounds__(kThreads, D == 64 && sizeof(T) == 2 ? 3 : 2) void k
     }
     if constexpr (kF32) {
       __syncthreads();
-      if (z != z) sh.redo = 1;
-      __syncthreads();
+      if (z != z) sh.redo = ~0u;
+    }
+    combine<D, kF32, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
+    __syncthreads();   // LDS is reused by the next slice
+    if constexpr (kF32)
       if (sh.redo) {   // from the P just written
         __threadfence_block();
-        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
-          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
-          if (i >= 0)
-            spmm_row<D, OutT, false>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
-        }
+        for_rows(sh.redo, s, [&](int i) {
+          spmm_row<D, OutT, false>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+        });
         __syncthreads();
-        continue;
       }
-    }
-    combine<D, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
-    __syncthreads();   // LDS is reused by the next slice
   }
 }
 

@@ -112,11 +112,14 @@ def test_fused_f32_first_scores_minus_infinity(gpu_lib, kind, params, L, heads, 
     if redo:
         V[:, :, 199] = math.inf
     a = splat.Acsr(splat.Pattern.named(kind, params, L))
-    O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
-    K[..., 0] = -math.inf
-    none = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
-    torch.cuda.synchronize()
-    assert _row_err(O[:, :2, :rows], ref[:, :, :rows]) <= F32_REL
+    Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
+    Kn = Kd.clone()
+    Kn[..., 0] = -math.inf
+    none = splat.sparse_mhsa_fwd(a, Qd, Kn, Vd, scale)
+    for O in (torch.empty_like(Qd), Qd):   # a tensor of its own, and Q's place
+        splat.sparse_mhsa_fwd(a, Qd, Kd, Vd, scale, O=O)
+        torch.cuda.synchronize()
+        assert _row_err(O[:, :2, :rows], ref[:, :, :rows]) <= F32_REL
     assert torch.isnan(none).all()
 
 
@@ -134,12 +137,33 @@ def test_fused_f32_large_values(gpu_lib, big, d):
     Q, K = torch.ones_like(K), 1e-3 * K
     for j in (130, 170, 200, 230):
         K[:, :, j] += 7.0 * math.log(2.0) / (scale * d)
-        V[:, :, j] *= big / V[:, :, j].abs().amax(-1, keepdim=True)
+        V[:, :, j, :8] *= big / V[:, :, j, :8].abs().amax(-1, keepdim=True)
     a = splat.Acsr(splat.Pattern.full(L))
     ref = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], om.dense_mask("full", {}, L), scale)
-    O = splat.sparse_mhsa_fwd(a, Q.cuda(), K.cuda(), V.cuda(), scale)
+    Qd = Q.cuda()
+    for O in (torch.empty_like(Qd), Qd):   # a tensor of its own, and Q's place
+        splat.sparse_mhsa_fwd(a, Qd, K.cuda(), V.cuda(), scale, O=O)
+        torch.cuda.synchronize()
+        assert _row_err(O[:, :2], ref) <= F32_REL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [1, 24])
+def test_rspmm_f32_large_values(gpu_lib, heads, d):
+    """Values that cancel key by key, near fp32's end: key after key the sums
+    stay finite, in another order they do not.  One head takes a wavefront per
+    row, 24 the slices; both layouts."""
+    splat = gpu_lib
+    L = 300
+    print(f"[gpu] rspmm f32 V = +-3e38 heads={heads} d={d}", flush=True)
+    a = splat.Acsr(splat.Pattern.full(L), columns=True)
+    P = torch.ones(1, heads, a.nnz, device="cuda")
+    V = torch.full((1, heads, L, d), 3e38, device="cuda")
+    V[:, :, 1::2] *= -1
+    O = splat.rspmm(a, P, V)
+    Oc = splat.rspmm_colmajor(a, P, V)
     torch.cuda.synchronize()
-    assert _row_err(O[:, :2], ref) <= F32_REL
+    assert (O == 0).all() and (Oc == 0).all()
 
 
 @pytest.mark.parametrize("d", [64, 128])
