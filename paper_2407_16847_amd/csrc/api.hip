@@ -286,13 +286,15 @@ splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
   CHECK(check_ptr(K, "K"));
   CHECK(check_rspmm(h, dtype, B, H, d, S, V, O, out_dtype, false));
   if (col) CHECK(check_transpose(h, B, H, S, Pt));
-  // The steps are done with Q and K before they write Pt and O, so these may
-  // share memory with them; one kernel's workgroups are not done together.
+  // The steps are done with Q and K before they write Pt and O, and with S
+  // before the column-major R-SpMM writes O, so these may share memory; one
+  // kernel's workgroups are not done together.
   const size_t elems = (size_t)B * H * a.L * d, in = elems * (dtype == SPLAT_BF16 ? 2 : 4);
   const size_t out = elems * (out_dtype == SPLAT_BF16 ? 2 : 4);
   const size_t vals = (size_t)B * H * a.nnz * 4;
   const bool shared = meet(O, out, Q, in) || meet(O, out, K, in) ||
-                      (col && (meet(Pt, vals, Q, in) || meet(Pt, vals, K, in)));
+                      (col && (meet(Pt, vals, Q, in) || meet(Pt, vals, K, in) ||
+                               meet(O, out, S, vals)));
   if (!shared && splat::chain_faster(h->dev, dtype, B * H, d)) {
     const bool values = keep_values || dtype != SPLAT_BF16;
     if (used_colmajor) *used_colmajor = col ? 1 : 0;

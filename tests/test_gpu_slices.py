@@ -257,6 +257,27 @@ def test_chain_output_over_an_input(gpu_lib, onto, noalloc, dtype):
     assert float(err.max()) <= 2 * tol
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("where", ["front", "back"])
+def test_chain_output_inside_scores(gpu_lib, where, dtype):
+    """On the column-major branch the last step reads Pt and V only, so O may
+    lie inside S: the same O as in a tensor of its own."""
+    splat = gpu_lib
+    L, d, heads = 1000, 64, 16
+    q, k, v = (x.cuda() for x in _qkv(L, d, heads, 22, dtype))
+    a = splat.Acsr(splat.Pattern.window(L, 100), columns=True)
+    ref, used = splat.sparse_mhsa_unfused(a, q, k, v, 0.125, alpha=0.0)
+    S = torch.empty(1, heads, a.nnz, device="cuda")
+    flat = S.view(-1).view(q.dtype)
+    O = (flat[:q.numel()] if where == "front" else flat[-q.numel():]).view(q.shape)
+    splat.sparse_mhsa_unfused(a, q, k, v, 0.125, alpha=0.0, S=S, O=O)
+    torch.cuda.synchronize()
+    assert used
+    tol = 2.0 ** -8 if dtype == "bf16" else F32_REL   # two orders of the same sums
+    err = (O.double() - ref.double()).abs().amax(-1) / ref.double().abs().amax(-1)
+    assert float(err.max()) <= 2 * tol
+
+
 def test_chain_without_keys(gpu_lib):
     """An empty mask and empty rows: O = 0, nothing else is written."""
     splat = gpu_lib
