@@ -388,8 +388,9 @@ def _like(x: torch.Tensor, name: str, Q: torch.Tensor, acsr: Acsr) -> None:
 
 
 def _new(ref: torch.Tensor, dtype: torch.dtype) -> torch.Tensor:
-    """An uninitialised contiguous tensor of ref's shape and device."""
-    if type(ref) is torch.Tensor:   # 0.6 us less than naming shape and device
+    """An uninitialised plain contiguous tensor of ref's shape and device."""
+    # 0.6 us less than naming shape and device; it would keep ref's axis names
+    if type(ref) is torch.Tensor and not ref.has_names():
         return torch.empty_like(ref, dtype=dtype, memory_format=torch.contiguous_format)
     return torch.empty(tuple(ref.shape), dtype=dtype, device=ref.device)
 
