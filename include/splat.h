@@ -432,6 +432,20 @@ splat_status splat_debug_bounds(uint32_t* flags, int32_t clear);
  */
 splat_status splat_debug_bounds_probe(int32_t kind, int32_t index, int32_t n, int32_t* result);
 
+/*
+ * splat_debug_route -- the kernel that a compute call takes (a debugging aid
+ * for tests of the library's choices; host only, also on a handle built without
+ * a GPU).  call: 0 = splat_rsddmm, 1 = splat_rspmm and splat_rspmm_colmajor,
+ * 2 = splat_sparse_mhsa_fwd, 3 = splat_sparse_mhsa_unfused and _noalloc with
+ * buffers that share no memory.  *route: 0 = a wavefront per row, 1 = a
+ * workgroup per 32 rows, 2 = a workgroup per 128 rows over the tile plan, 3 =
+ * the chain in one kernel, 4 = its single steps.  *sets (if non-NULL): the sets
+ * of wavefronts that share out a row group's tiles in the fused bf16 call, 1
+ * elsewhere.  Which launches take which kernel may change between versions.
+ */
+splat_status splat_debug_route(splat_acsr_t h, int32_t call, splat_dtype dtype, int32_t B,
+                               int32_t H, int32_t d, int32_t* route, int32_t* sets);
+
 /* Message of the calling thread's last non-OK status ("" if none). */
 const char* splat_last_error(void);
 

@@ -134,6 +134,7 @@ def _open(path: str) -> ctypes.CDLL:
         "splat_rspmm_colmajor": [vp, i32, i32, i32, i32, vp, vp, vp, i32, vp],
         "splat_sparse_mhsa_unfused": [vp, i32, i32, i32, i32, vp, vp, vp, f32, vp, vp, vp, i32, f32,
                                       P(i32), vp],
+        "splat_debug_route": [vp, i32, i32, i32, i32, i32, P(i32), P(i32)],
         "splat_debug_bounds": [P(ctypes.c_uint32), i32],
         "splat_debug_bounds_probe": [i32, i32, i32, P(i32)],
     }
@@ -350,6 +351,19 @@ class Acsr:
 
 # ---------------------------------------------------------------------------
 _DT = {torch.float32: F32, torch.bfloat16: BF16}
+
+_CALLS = ("rsddmm", "rspmm", "sparse_mhsa_fwd", "sparse_mhsa_unfused")
+_ROUTES = ("rows", "slices", "tiles", "chain", "steps")
+
+
+def route(acsr: Acsr, call: str, dtype: torch.dtype, B: int, H: int, d: int) -> Tuple[str, int]:
+    """(kernel, sets of wavefronts) that a call takes (splat_debug_route): for
+    tests of the choice; needs no GPU."""
+    r, n = ctypes.c_int32(), ctypes.c_int32()
+    _check(acsr._lib.splat_debug_route(acsr.handle, _CALLS.index(call), _DT[dtype], B, H, d,
+                                       ctypes.byref(r), ctypes.byref(n)))
+    return _ROUTES[r.value], n.value
+
 
 
 def _dense(x: torch.Tensor, name: str, acsr: Acsr, d: Optional[int] = None):

@@ -41,6 +41,30 @@ splat_status fail(splat_status s, const char* fmt, ...) {
 
 splat_status ok() { return SPLAT_OK; }
 
+// What the launches choose their kernels by (also of a host-only handle).
+void plan_sizes(splat_acsr* h) {
+  const HostAcsr& a = h->host;
+  h->dev.L = a.L;
+  h->dev.nnz = a.nnz;
+  h->dev.max_row_nnz = a.max_row_nnz;
+  h->dev.n_groups = (int32_t)a.groups.size();
+  h->dev.computed = a.computed;
+  h->dev.max_slice_tiles = 0;
+  h->dev.n_tiles = (int32_t)a.tiles.size();
+  h->dev.max_group_tiles = 0;
+  for (const splat::Group& g : a.groups)
+    h->dev.max_group_tiles = std::max(h->dev.max_group_tiles, g.tile_end - g.tile_begin);
+  h->dev.rows_aligned = a.nnz % 32 == 0;
+  for (int32_t p : a.row_ptr) h->dev.rows_aligned = h->dev.rows_aligned && p % 32 == 0;
+  for (const splat::Group& g : a.groups)
+    for (int w = 0; w < splat::kWavesPerGroup; ++w) {
+      int32_t n = 0;
+      for (int32_t t = g.tile_begin; t < g.tile_end; ++t)
+        n += ((a.tiles[t].flags >> (splat::kWaveShift + 2 * w)) & 3) != splat::kWaveEmpty;
+      h->dev.max_slice_tiles = std::max(h->dev.max_slice_tiles, n);
+    }
+}
+
 // One allocation holds every metadata array, each 256-byte aligned.
 splat_status upload(splat_acsr* h) {
   int n = 0;
@@ -102,25 +126,6 @@ splat_status upload(splat_acsr* h) {
   }
   h->dmem = mem;
   h->device = dev;
-  h->dev.L = a.L;
-  h->dev.nnz = a.nnz;
-  h->dev.max_row_nnz = a.max_row_nnz;
-  h->dev.n_groups = (int32_t)a.groups.size();
-  h->dev.computed = a.computed;
-  h->dev.max_slice_tiles = 0;
-  h->dev.n_tiles = (int32_t)a.tiles.size();
-  h->dev.max_group_tiles = 0;
-  for (const splat::Group& g : a.groups)
-    h->dev.max_group_tiles = std::max(h->dev.max_group_tiles, g.tile_end - g.tile_begin);
-  h->dev.rows_aligned = a.nnz % 32 == 0;
-  for (int32_t p : a.row_ptr) h->dev.rows_aligned = h->dev.rows_aligned && p % 32 == 0;
-  for (const splat::Group& g : a.groups)
-    for (int w = 0; w < splat::kWavesPerGroup; ++w) {
-      int32_t n = 0;
-      for (int32_t t = g.tile_begin; t < g.tile_end; ++t)
-        n += ((a.tiles[t].flags >> (splat::kWaveShift + 2 * w)) & 3) != splat::kWaveEmpty;
-      h->dev.max_slice_tiles = std::max(h->dev.max_slice_tiles, n);
-    }
   h->dev.row_ptr = (const int32_t*)dst[0];
   h->dev.runs = (const splat::RowRuns*)dst[1];
   h->dev.rows = (const int32_t*)dst[2];
@@ -136,6 +141,7 @@ splat_status finish_build(splat_acsr* h, splat_status s, const std::string& err,
     delete h;
     return fail(s, "%s", err.c_str());
   }
+  plan_sizes(h);
   s = upload(h);
   if (s != SPLAT_OK) {
     delete h;
@@ -148,10 +154,16 @@ splat_status finish_build(splat_acsr* h, splat_status s, const std::string& err,
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Validation shared by the compute calls.  Returns SPLAT_OK or the failure.
-splat_status check_handle(splat_acsr_t h, int32_t B, int32_t H) {
-  if (!h) return fail(SPLAT_ERR_INVALID_ARG, "ACSR handle is NULL");
+splat_status check_batch(int32_t B, int32_t H) {
   if (B < 1 || H < 1 || (int64_t)B * H > 65535)
     return fail(SPLAT_ERR_INVALID_ARG, "B and H must be >= 1 with B*H <= 65535 (got B=%d, H=%d)", B, H);
+  return SPLAT_OK;
+}
+
+splat_status check_handle(splat_acsr_t h, int32_t B, int32_t H) {
+  if (!h) return fail(SPLAT_ERR_INVALID_ARG, "ACSR handle is NULL");
+  splat_status s = check_batch(B, H);
+  if (s != SPLAT_OK) return s;
   if (h->device < 0)
     return fail(SPLAT_ERR_NO_DEVICE, "the ACSR handle was built without a GPU");
   int dev = -1;
@@ -295,7 +307,7 @@ splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
   const bool shared = meet(O, out, Q, in) || meet(O, out, K, in) ||
                       (col && (meet(Pt, vals, Q, in) || meet(Pt, vals, K, in) ||
                                meet(O, out, S, vals)));
-  if (!shared && splat::chain_faster(h->dev, dtype, B * H, d)) {
+  if (!shared && splat::unfused_route(h->dev, dtype, B * H, d) == splat::kRouteChain) {
     const bool values = keep_values || dtype != SPLAT_BF16;
     if (used_colmajor) *used_colmajor = col ? 1 : 0;
     return launched(splat::launch_chain(h->dev, dtype, B * H, d, Q, K, V, scale,
@@ -637,6 +649,27 @@ splat_status splat_sparse_mhsa_unfused_noalloc(splat_acsr_t h, splat_dtype dtype
   return run_unfused(h, dtype, B, H, d, Q, K, V, scale, (float*)base,
                      col ? (float*)(base + s_bytes) : nullptr, O, out_dtype, alpha, used_colmajor,
                      (hipStream_t)stream, false);
+}
+
+splat_status splat_debug_route(splat_acsr_t h, int32_t call, splat_dtype dtype, int32_t B,
+                               int32_t H, int32_t d, int32_t* route, int32_t* sets) {
+  if (!h || !route) return fail(SPLAT_ERR_INVALID_ARG, "handle and route must be non-NULL");
+  CHECK(check_batch(B, H));
+  CHECK(check_dtype(dtype, "dtype"));
+  CHECK(check_d(d));
+  if (call < 0 || call > 3) return fail(SPLAT_ERR_INVALID_ARG, "call %d is not 0..3", call);
+  const DevAcsr& a = h->dev;
+  const int BH = B * H;
+  int32_t n = 1;
+  if (call == 0) *route = splat::rsddmm_route(a, dtype, BH, d);
+  if (call == 1) *route = splat::rspmm_route(a, dtype, BH, d);
+  if (call == 2) {
+    *route = dtype == SPLAT_BF16 ? splat::kRouteTiles : splat::fused_f32_route(a, BH, d);
+    if (dtype == SPLAT_BF16) n = splat::fused_mfma_sets(a, BH, d);
+  }
+  if (call == 3) *route = splat::unfused_route(a, dtype, BH, d);
+  if (sets) *sets = n;
+  return ok();
 }
 
 splat_status splat_debug_bounds(uint32_t* flags, int32_t clear) {

@@ -430,6 +430,8 @@ __global__ __launch_bounds__(kThreads * NSET, D == 64 ? 4 : 2) void k_fused_mfma
   }
 }
 
+}  // namespace
+
 // How many sets of wavefronts share out a group's tiles: one, unless the longest
 // group walked tile by tile (0.84 us each at d = 64, 1.57 at 128) outlasts the
 // launch's tiles at throughput (2.5 and 5.7 ns each).  Measured, 1 / 2 / 4 sets:
@@ -438,12 +440,14 @@ __global__ __launch_bounds__(kThreads * NSET, D == 64 ? 4 : 2) void k_fused_mfma
 // heads 72 / 60 / 75, 64 heads 95 / 107; strided+local 128, L = 2048, 24 heads
 // (5 tiles) 11.3 / 12.5; full, L = 512, 8 heads 10.2 / 9.2 / 9.9.  Two sets
 // of d = 128 and four of d = 64 fill a CU's LDS and wavefronts.
-inline int fused_sets(const DevAcsr& a, int BH, int d) {
+int fused_mfma_sets(const DevAcsr& a, int BH, int d) {
   const double chain = (d == 64 ? 0.84 : 1.57) * a.max_group_tiles;
   const double all = (d == 64 ? 2.5e-3 : 5.7e-3) * a.n_tiles * BH;
   if (a.max_group_tiles < 8 || chain <= all) return 1;
   return d == 64 && a.max_group_tiles >= 16 && chain / 2 > all ? 4 : 2;
 }
+
+namespace {
 
 template <int D, typename OutT, int NSET>
 hipError_t allow_lds() {
@@ -463,7 +467,7 @@ hipError_t fused_launch(const DevAcsr& a, int BH, const void* Q, const void* K, 
 template <int D, typename OutT>
 hipError_t fused_out(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                      float sl2, void* O, hipStream_t st) {
-  const int sets = fused_sets(a, BH, D);
+  const int sets = fused_mfma_sets(a, BH, D);
   if constexpr (D == 64)
     if (sets == 4) return fused_launch<D, OutT, 4>(a, BH, Q, K, V, sl2, O, st);
   return sets >= 2 ? fused_launch<D, OutT, 2>(a, BH, Q, K, V, sl2, O, st)

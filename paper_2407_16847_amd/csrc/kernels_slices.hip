@@ -1263,6 +1263,42 @@ bool rspmm_bf16_slices(const DevAcsr& a, const Size& z) {
   return slc < tiles;
 }
 
+// bf16, one kernel against the steps: blocked 64, L = 1024, 16 heads 9.9 /
+// 26.5 us, window 512 + 64 global, L = 4096, 64 heads 569 / 1006, window 4, L =
+// 4096, 64 heads 85 / 85; only where nearly all computed scores are outside a
+// mask of many slices do three launches pay (window 2: 85 / 82).  fp32: strided+
+// local 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
+bool chain_faster(const DevAcsr& a, int dtype, int BH, int d) {
+  const Size z(a, BH, d);
+  if (dtype != 0) return !(z.C > 16 * z.E && z.NS > 4096);
+  const double steps =
+      7.8 + 1.6e-6 * z.E +
+      (rsddmm_rows_faster(z) ? rsddmm_rows_us(z) : rsddmm_slices_us(z)) +
+      fmin(rspmm_rows_us(z), rspmm_slices_us(z));
+  return 3.2 + slices_us(z, 10, 4.2, (z.w + 1) / 2 * (1.2 + 5.6 * z.chain)) < steps;
+}
+
+}  // namespace
+
+Route rsddmm_route(const DevAcsr& a, int dtype, int BH, int d) {
+  const Size z(a, BH, d);
+  if (dtype != 0) return rsddmm_bf16_slices(a, z) ? kRouteSlices : kRouteTiles;
+  return rsddmm_rows_faster(z) ? kRouteRows : kRouteSlices;
+}
+Route rspmm_route(const DevAcsr& a, int dtype, int BH, int d) {
+  const Size z(a, BH, d);
+  if (dtype != 0) return rspmm_bf16_slices(a, z) ? kRouteSlices : kRouteTiles;
+  return rspmm_rows_faster(z) ? kRouteRows : kRouteSlices;
+}
+Route fused_f32_route(const DevAcsr& a, int BH, int d) {
+  return fused_rows_faster(Size(a, BH, d)) ? kRouteRows : kRouteSlices;
+}
+Route unfused_route(const DevAcsr& a, int dtype, int BH, int d) {
+  return chain_faster(a, dtype, BH, d) ? kRouteChain : kRouteSteps;
+}
+
+namespace {
+
 // Grid of the row kernels: four rows per workgroup.
 inline dim3 row_grid(const DevAcsr& a, int BH) {
   return dim3((unsigned)BH, (unsigned)((a.L + 3) / 4));
@@ -1280,7 +1316,7 @@ hipError_t fused_rows(const DevAcsr& a, int BH, const void* Q, const void* K, co
 template <typename T, int D>
 hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                    float scale, void* O, int out_dtype, hipStream_t st) {
-  if (fused_rows_faster(Size(a, BH, D)))
+  if (fused_f32_route(a, BH, D) == kRouteRows)
     return out_dtype == 0 ? fused_rows<D, float>(a, BH, Q, K, V, scale, O, st)
                           : fused_rows<D, __bf16>(a, BH, Q, K, V, scale, O, st);
   if (out_dtype == 0)
@@ -1297,11 +1333,12 @@ hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const
 template <typename T, int D>
 hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, float scale, float* S,
                     hipStream_t st) {
-  if (sizeof(T) == 4 && rsddmm_rows_faster(Size(a, BH, D))) {
-    hipLaunchKernelGGL((k_rsddmm_rows<D>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr, a.runs, a.L,
-                       a.nnz, (const float*)Q, (const float*)K, scale, S);
-    return hipGetLastError();
-  }
+  if constexpr (sizeof(T) == 4)
+    if (rsddmm_route(a, 0, BH, D) == kRouteRows) {
+      hipLaunchKernelGGL((k_rsddmm_rows<D>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr, a.runs, a.L,
+                         a.nnz, (const float*)Q, (const float*)K, scale, S);
+      return hipGetLastError();
+    }
   hipLaunchKernelGGL((k_rsddmm_slices<T, D>), slice_grid(a, BH), dim3(kThreads), 0, st, a.groups,
                      a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, a.nnz, slices(a),
                      (const T*)Q, (const T*)K, scale, S);
@@ -1311,11 +1348,12 @@ hipError_t rsddmm_d(const DevAcsr& a, int BH, const void* Q, const void* K, floa
 template <typename T, int D, typename OutT, bool COL>
 hipError_t rspmm_d(const DevAcsr& a, int BH, const float* P, const void* V, void* O,
                    hipStream_t st) {
-  if (sizeof(T) == 4 && rspmm_rows_faster(Size(a, BH, D))) {
-    hipLaunchKernelGGL((k_rspmm_rows<D, OutT, COL>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr,
-                       a.runs, a.cols, a.L, a.nnz, P, (const float*)V, (OutT*)O);
-    return hipGetLastError();
-  }
+  if constexpr (sizeof(T) == 4)
+    if (rspmm_route(a, 0, BH, D) == kRouteRows) {
+      hipLaunchKernelGGL((k_rspmm_rows<D, OutT, COL>), dim3(a.L, BH), dim3(64), 0, st, a.row_ptr,
+                         a.runs, a.cols, a.L, a.nnz, P, (const float*)V, (OutT*)O);
+      return hipGetLastError();
+    }
   hipLaunchKernelGGL((k_rspmm_slices<T, D, OutT, COL>), slice_grid(a, BH), dim3(kThreads), 0, st,
                      a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.cols, a.L, a.nnz,
                      slices(a), P, (const T*)V, (OutT*)O);
@@ -1389,7 +1427,7 @@ hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, cons
 hipError_t launch_rsddmm(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
                          float scale, float* S, hipStream_t st) {
   if (dtype != 0) {
-    if (!rsddmm_bf16_slices(a, Size(a, BH, d)))
+    if (rsddmm_route(a, dtype, BH, d) == kRouteTiles)
       return launch_rsddmm_tiles(a, BH, d, Q, K, scale, S, st);
     return d == 64 ? rsddmm_d<__bf16, 64>(a, BH, Q, K, scale, S, st)
                    : rsddmm_d<__bf16, 128>(a, BH, Q, K, scale, S, st);
@@ -1401,28 +1439,13 @@ hipError_t launch_rsddmm(const DevAcsr& a, int dtype, int BH, int d, const void*
 hipError_t launch_rspmm(const DevAcsr& a, int dtype, int BH, int d, const float* P, const void* V,
                         void* O, int out_dtype, bool colmajor, hipStream_t st) {
   if (dtype != 0) {
-    if (!rspmm_bf16_slices(a, Size(a, BH, d)))
+    if (rspmm_route(a, dtype, BH, d) == kRouteTiles)
       return launch_rspmm_tiles(a, BH, d, P, V, O, out_dtype, colmajor, st);
     return colmajor ? rspmm_t<__bf16, true>(a, BH, d, P, V, O, out_dtype, st)
                     : rspmm_t<__bf16, false>(a, BH, d, P, V, O, out_dtype, st);
   }
   return colmajor ? rspmm_t<float, true>(a, BH, d, P, V, O, out_dtype, st)
                   : rspmm_t<float, false>(a, BH, d, P, V, O, out_dtype, st);
-}
-
-// bf16, one kernel against the steps: blocked 64, L = 1024, 16 heads 9.9 /
-// 26.5 us, window 512 + 64 global, L = 4096, 64 heads 569 / 1006, window 4, L =
-// 4096, 64 heads 85 / 85; only where nearly all computed scores are outside a
-// mask of many slices do three launches pay (window 2: 85 / 82).  fp32: strided+
-// local 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
-bool chain_faster(const DevAcsr& a, int dtype, int BH, int d) {
-  const Size z(a, BH, d);
-  if (dtype != 0) return !(z.C > 16 * z.E && z.NS > 4096);
-  const double steps =
-      7.8 + 1.6e-6 * z.E +
-      (rsddmm_rows_faster(z) ? rsddmm_rows_us(z) : rsddmm_slices_us(z)) +
-      fmin(rspmm_rows_us(z), rspmm_slices_us(z));
-  return 3.2 + slices_us(z, 10, 4.2, (z.w + 1) / 2 * (1.2 + 5.6 * z.chain)) < steps;
 }
 
 hipError_t launch_chain(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,

@@ -36,6 +36,16 @@ __device__ __forceinline__ int col_pos(const ColRun& c, int row) {
   return c.ptr + (int)__builtin_rintf(t);
 }
 
+// The kernels a launch chooses from: a wavefront per row, a workgroup per 32
+// rows, a workgroup per 128 rows over the tile plan; the unfused chain in one
+// kernel, or its single steps.
+enum Route : int32_t { kRouteRows, kRouteSlices, kRouteTiles, kRouteChain, kRouteSteps };
+Route rsddmm_route(const DevAcsr& a, int dtype, int BH, int d);
+Route rspmm_route(const DevAcsr& a, int dtype, int BH, int d);   // both layouts
+Route fused_f32_route(const DevAcsr& a, int BH, int d);
+int fused_mfma_sets(const DevAcsr& a, int BH, int d);   // sets of wavefronts per tile group
+Route unfused_route(const DevAcsr& a, int dtype, int BH, int d);
+
 // Every launcher enqueues on `st` and returns the launch status.
 // dtype / out dtype: 0 = fp32, 1 = bf16.
 
@@ -51,8 +61,6 @@ hipError_t launch_rspmm(const DevAcsr& a, int dtype, int BH, int d, const float*
 
 // The unfused chain in one kernel: P (row-major values), Pt (their
 // column-major copy, or null) and O.  P null: O alone (bf16 inputs only).
-// chain_faster: whether it beats the three or four launches of the steps.
-bool chain_faster(const DevAcsr& a, int dtype, int BH, int d);
 hipError_t launch_chain(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
                         const void* V, float scale, float* P, float* Pt, void* O, int out_dtype,
                         hipStream_t st);

@@ -41,6 +41,14 @@ CASES = [
     ("strided_local", {"local": 4, "stride": 64}, 600, 2),
     ("window_global", {"w": 3, "n_global": 1}, 4200, 1),
 ]
+# heads enough for the fp32 R-SpMM over slices.  Which kernels the lists of this
+# file reach is checked without a GPU in test_host_routes.py.
+STEPS = CASES + [
+    ("full", {}, 97, 120), ("blocked", {"block": 33}, 300, 100),
+    ("dilated", {"w": 100, "dilation": 3}, 700, 40),
+    ("strided_local", {"local": 40, "stride": 33}, 500, 100),
+]
+NON_FINITE = [CASES[5], CASES[6], CASES[7], CASES[8], CASES[10], STEPS[-3], STEPS[-2], STEPS[-1]]
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -63,7 +71,7 @@ def test_fused_f32(gpu_lib, kind, params, L, heads, d):
 
 @pytest.mark.parametrize("where", ["K", "V"])
 @pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
-@pytest.mark.parametrize("kind,params,L,heads", [CASES[6], CASES[7], CASES[8], CASES[10]])
+@pytest.mark.parametrize("kind,params,L,heads", NON_FINITE)
 def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, where):
     """A key with an infinity or a NaN changes only the rows that have it."""
     splat = gpu_lib
@@ -73,11 +81,12 @@ def test_f32_rows_see_only_their_keys(gpu_lib, kind, params, L, heads, value, wh
     j = L // 2
     (K if where == "K" else V)[:, :, j, 3] = value
     M = om.dense_mask(kind, params, L)
-    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    a = splat.Acsr(splat.Pattern.named(kind, params, L), columns=True)
     Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
-    S = splat.rsddmm(a, Qd, Kd, scale)
+    P = splat.row_softmax(a, splat.rsddmm(a, Qd, Kd, scale))
     outs = {"fused": splat.sparse_mhsa_fwd(a, Qd, Kd, Vd, scale),
-            "steps": splat.rspmm(a, splat.row_softmax(a, S), Vd),
+            "steps": splat.rspmm(a, P, Vd),
+            "columns": splat.rspmm_colmajor(a, splat.transpose_colmajor(a, P), Vd),
             "unfused": splat.sparse_mhsa_unfused(a, Qd, Kd, Vd, scale)[0]}
     torch.cuda.synchronize()
     clean = torch.from_numpy(~M[:, j])
@@ -167,17 +176,20 @@ def test_rspmm_f32_large_values(gpu_lib, heads, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("kind,params,L,heads", CASES)
+@pytest.mark.parametrize("kind,params,L,heads", STEPS)
 def test_steps_f32(gpu_lib, kind, params, L, heads, d):
     splat = gpu_lib
     print(f"[gpu] steps f32 {kind} {params} L={L} heads={heads} d={d}", flush=True)
     scale = 1.0 / math.sqrt(d)
     Q, K, V = _qkv(L, d, heads, L + 2 * d)
     M = om.dense_mask(kind, params, L)
-    a = splat.Acsr(splat.Pattern.named(kind, params, L))
+    a = splat.Acsr(splat.Pattern.named(kind, params, L), columns=True)
     S = splat.rsddmm(a, Q.cuda(), K.cuda(), scale)
     P = splat.row_softmax(a, S)
     O = splat.rspmm(a, P, V.cuda())
+    if a.info()["columns"] == 1:
+        Oc = splat.rspmm_colmajor(a, splat.transpose_colmajor(a, P), V.cuda())
+        assert torch.equal(Oc, O)
     torch.cuda.synchronize()
     ref, _, _ = oa.masked_attention(Q[:, :2], K[:, :2], V[:, :2], M, scale, want_csr=True)
     assert _row_err(O[:, :2], ref) <= F32_REL
@@ -298,7 +310,8 @@ def test_chain_without_keys(gpu_lib):
 @pytest.mark.parametrize("heads", [2, 400])
 @pytest.mark.parametrize("kind,params,L", [c[:3] for c in CASES[:-1]])
 def test_steps_bf16(gpu_lib, kind, params, L, heads, d):
-    """Few heads take the slices, many the 128-row tile kernels."""
+    """Two heads take the slices, 400 the 128-row tile kernels (R-SDDMM at d = 64
+    the slices also for 400 heads of short or thin masks)."""
     splat = gpu_lib
     print(f"[gpu] steps bf16 {kind} {params} L={L} heads={heads} d={d}", flush=True)
     scale = 1.0 / math.sqrt(d)
@@ -355,12 +368,15 @@ def test_binding_streams_and_outputs(gpu_lib):
 # groups of 7 (one set of wavefronts), 9, 13 (two), 17 and 23 tiles (four at d =
 # 64), a last group of few rows, empty tiles; scores around 0, and rising with
 # the key so that the sets end with references far apart
-@pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("rise", [0.0, 12.0])
-@pytest.mark.parametrize("kind,params,L", [
+SETS = [
     ("full", {}, 448), ("full", {}, 520), ("full", {}, 777), ("full", {}, 1088),
     ("window", {"w": 500}, 1450), ("window_global", {"w": 30, "n_global": 3}, 1300),
-    ("strided_local", {"local": 600, "stride": 100}, 900)])
+    ("strided_local", {"local": 600, "stride": 100}, 900)]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rise", [0.0, 12.0])
+@pytest.mark.parametrize("kind,params,L", SETS)
 def test_fused_sets(gpu_lib, kind, params, L, rise, d):
     splat = gpu_lib
     print(f"[gpu] fused sets {kind} {params} L={L} rise={rise} d={d}", flush=True)

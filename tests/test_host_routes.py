@@ -1,0 +1,80 @@
+"""Which kernels the cases of the GPU tests reach (host only: the choice is made
+from the plan's sizes), so that a change of the choice cannot leave a kernel
+untested."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2407_16847_amd as splat
+import test_gpu_slices as gpu
+
+F32, BF16 = torch.float32, torch.bfloat16
+
+
+def _acsr(kind, params, L):
+    return splat.Acsr(splat.Pattern.named(kind, params, L), columns=True)
+
+
+def _reached(call, dtype, cases, d, heads=None):
+    """{(route, sets)}; cases without the heads are taken with each of `heads`."""
+    out = set()
+    for kind, params, L, *h in cases:
+        a = _acsr(kind, params, L)
+        for n in heads or h:
+            out.add(splat.route(a, call, dtype, 1, n, d))
+    return out
+
+
+def _names(*args, **kw):
+    return {r for r, _ in _reached(*args, **kw)}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_cases(d):
+    assert _names("sparse_mhsa_fwd", F32, gpu.CASES, d) == {"rows", "slices"}
+    for call in ("rsddmm", "rspmm"):
+        assert _names(call, F32, gpu.STEPS, d) == {"rows", "slices"}
+    assert _names("sparse_mhsa_unfused", F32, gpu.CHAIN, d) == {"chain", "steps"}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_column_major_cases(d):
+    """The column-major R-SpMM takes the row-major call's kernel, and needs
+    masks whose columns are single runs; stepped columns are addressed apart."""
+    cols = [c for c in gpu.STEPS if _acsr(*c[:3]).info()["columns"] == 1]
+    for kinds in ({"window", "blocked", "strided_local", "full"}, {"dilated"}):
+        assert _names("rspmm", F32, [c for c in cols if c[0] in kinds], d) == {"rows", "slices"}
+
+
+def test_non_finite_cases():
+    for call in ("sparse_mhsa_fwd", "rspmm"):
+        assert _names(call, F32, gpu.NON_FINITE, 64) == {"rows", "slices"}
+    assert _names("sparse_mhsa_unfused", F32, gpu.NON_FINITE, 64) == {"chain", "steps"}
+    # all four results are compared: every mask has the column-major layout
+    assert all(_acsr(*c[:3]).info()["columns"] == 1 for c in gpu.NON_FINITE)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_bf16_cases(d):
+    masks = [c[:3] for c in gpu.CASES[:-1]]
+    for call in ("rsddmm", "rspmm"):
+        assert _names(call, BF16, masks, d, heads=[2]) == {"slices"}
+        assert "tiles" in _names(call, BF16, masks, d, heads=[400])
+    assert _names("rspmm", BF16, masks, d, heads=[400]) == {"tiles"}
+    assert _names("sparse_mhsa_unfused", BF16, gpu.CHAIN, d) == {"chain", "steps"}
+    sets = {("tiles", 1), ("tiles", 2)} | ({("tiles", 4)} if d == 64 else set())
+    assert _reached("sparse_mhsa_fwd", BF16, gpu.SETS, d, heads=[3]) == sets
+
+
+def test_argument_checks():
+    a = _acsr("window", {"w": 5}, 65)
+    lib, r = splat.load(), ctypes.c_int32(7)
+    bad = [(None, 0, 0, 1, 1, 64, ctypes.byref(r)), (a.handle, 0, 0, 1, 1, 64, None),
+           (a.handle, 4, 0, 1, 1, 64, ctypes.byref(r)), (a.handle, -1, 0, 1, 1, 64, ctypes.byref(r)),
+           (a.handle, 0, 2, 1, 1, 64, ctypes.byref(r)), (a.handle, 0, 0, 0, 1, 64, ctypes.byref(r))]
+    for args in bad:
+        assert lib.splat_debug_route(*args, None) == 1          # INVALID_ARG
+    assert lib.splat_debug_route(a.handle, 0, 0, 1, 1, 96, ctypes.byref(r), None) == 2   # UNSUPPORTED
+    assert r.value == 7                                          # nothing written
+    assert lib.splat_debug_route(a.handle, 0, 0, 1, 1, 64, ctypes.byref(r), None) == 0
