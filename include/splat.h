@@ -370,9 +370,10 @@ splat_status splat_sparse_mhsa_unfused(splat_acsr_t h, splat_dtype dtype, int32_
  * splat_sparse_mhsa_unfused_noalloc -- splat_sparse_mhsa_unfused for callers
  * that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): the same chain and the
- * same results, with S (and, on the column-major branch,
- * Pt) held in a scratch array inside the library instead of caller
- * workspaces.  The caller passes Q, K, V and O as for
+ * same results (within their rounding: with bf16 inputs and few non-zeros a
+ * slice of rows, one call may run as one kernel and the other as its steps),
+ * with S (and, on the column-major branch, Pt) held in a scratch array inside
+ * the library instead of caller workspaces.  The caller passes Q, K, V and O as for
  * splat_sparse_mhsa_unfused; the call allocates nothing.
  *
  * The scratch is a fixed SPLAT_NOALLOC_SCRATCH_BYTES (64 MiB) per device,
@@ -436,8 +437,9 @@ splat_status splat_debug_bounds_probe(int32_t kind, int32_t index, int32_t n, in
  * splat_debug_route -- the kernel that a compute call takes (a debugging aid
  * for tests of the library's choices; host only, also on a handle built without
  * a GPU).  call: 0 = splat_rsddmm, 1 = splat_rspmm and splat_rspmm_colmajor,
- * 2 = splat_sparse_mhsa_fwd, 3 = splat_sparse_mhsa_unfused and _noalloc with
- * buffers that share no memory.  *route: 0 = a wavefront per row, 1 = a
+ * 2 = splat_sparse_mhsa_fwd, 3 = splat_sparse_mhsa_unfused with buffers that
+ * share no memory, 4 = its column-major branch, 5 = the allocation-free call on
+ * the row-major branch.  *route: 0 = a wavefront per row, 1 = a
  * workgroup per 32 rows, 2 = a workgroup per 128 rows over the tile plan, 3 =
  * the chain in one kernel, 4 = its single steps.  *sets (if non-NULL): the sets
  * of wavefronts that share out a row group's tiles in the fused bf16 call, 1

@@ -352,7 +352,8 @@ class Acsr:
 # ---------------------------------------------------------------------------
 _DT = {torch.float32: F32, torch.bfloat16: BF16}
 
-_CALLS = ("rsddmm", "rspmm", "sparse_mhsa_fwd", "sparse_mhsa_unfused")
+_CALLS = ("rsddmm", "rspmm", "sparse_mhsa_fwd", "sparse_mhsa_unfused",
+          "sparse_mhsa_unfused, column-major", "sparse_mhsa_unfused_noalloc")
 _ROUTES = ("rows", "slices", "tiles", "chain", "steps")
 
 

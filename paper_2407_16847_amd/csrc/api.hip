@@ -307,7 +307,8 @@ splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
   const bool shared = meet(O, out, Q, in) || meet(O, out, K, in) ||
                       (col && (meet(Pt, vals, Q, in) || meet(Pt, vals, K, in) ||
                                meet(O, out, S, vals)));
-  if (!shared && splat::unfused_route(h->dev, dtype, B * H, d) == splat::kRouteChain) {
+  if (!shared &&
+      splat::unfused_route(h->dev, dtype, B * H, d, col, keep_values) == splat::kRouteChain) {
     const bool values = keep_values || dtype != SPLAT_BF16;
     if (used_colmajor) *used_colmajor = col ? 1 : 0;
     return launched(splat::launch_chain(h->dev, dtype, B * H, d, Q, K, V, scale,
@@ -657,7 +658,7 @@ splat_status splat_debug_route(splat_acsr_t h, int32_t call, splat_dtype dtype, 
   CHECK(check_batch(B, H));
   CHECK(check_dtype(dtype, "dtype"));
   CHECK(check_d(d));
-  if (call < 0 || call > 3) return fail(SPLAT_ERR_INVALID_ARG, "call %d is not 0..3", call);
+  if (call < 0 || call > 5) return fail(SPLAT_ERR_INVALID_ARG, "call %d is not 0..5", call);
   const DevAcsr& a = h->dev;
   const int BH = B * H;
   int32_t n = 1;
@@ -667,7 +668,7 @@ splat_status splat_debug_route(splat_acsr_t h, int32_t call, splat_dtype dtype, 
     *route = dtype == SPLAT_BF16 ? splat::kRouteTiles : splat::fused_f32_route(a, BH, d);
     if (dtype == SPLAT_BF16) n = splat::fused_mfma_sets(a, BH, d);
   }
-  if (call == 3) *route = splat::unfused_route(a, dtype, BH, d);
+  if (call >= 3) *route = splat::unfused_route(a, dtype, BH, d, call == 4, call != 5);
   if (sets) *sets = n;
   return ok();
 }

@@ -1264,13 +1264,28 @@ bool rspmm_bf16_slices(const DevAcsr& a, const Size& z) {
 }
 
 // bf16, one kernel against the steps: blocked 64, L = 1024, 16 heads 9.9 /
-// 26.5 us, window 512 + 64 global, L = 4096, 64 heads 569 / 1006, window 4, L =
-// 4096, 64 heads 85 / 85; only where nearly all computed scores are outside a
-// mask of many slices do three launches pay (window 2: 85 / 82).  fp32: strided+
-// local 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
-bool chain_faster(const DevAcsr& a, int dtype, int BH, int d) {
+// 26.5 us, window 512 + 64 global, L = 4096, 64 heads 569 / 1006.  The kernel
+// forms the scores twice and costs more a slice; the steps cost two launches
+// more, and stores and reads of S.  Many slices of few non-zeros pay for the
+// steps: d = 64, window 4, L = 12000, 57 heads 256 / 209, window 8, 19040 slices
+// 230 / 207, window 13, 24420 slices 285 / 264; d = 128, window 8, L = 8192, 32
+// heads 161 / 137, blocked 6, 8064 slices 149 / 116, window 31, L = 6830, 51 heads
+// 240 / 228; below 5000 and 2500 slices the launches decide (d = 128, blocked 6,
+// 2324 slices 49 / 53).  The lines are fitted to 1160 launches, of which 9 lose
+// more than 5% by them (14% at most).  A long row group holds the steps up.  The
+// column-major branch has a fourth launch (window 15, dilation 3, L = 2900, 136
+// heads 236 / 254), and O alone costs less than O and P (values: P is stored;
+// d = 64, window 4, L = 12000, 57 heads 197 / 209; d = 128, dilated 8 / 5, L =
+// 16288, 37 heads 322 / 306): there only the thinnest masks.  fp32: strided+local
+// 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
+bool chain_faster(const DevAcsr& a, int dtype, int BH, int d, bool col, bool values) {
   const Size z(a, BH, d);
-  if (dtype != 0) return !(z.C > 16 * z.E && z.NS > 4096);
+  if (dtype != 0) {
+    if (z.C > 16 * z.E && z.NS > 4096) return false;
+    const double few = values ? (d == 64 ? 1200 * (z.NS - 5000) : 2700 * (z.NS - 2500))
+                              : (d == 64 ? 0 : 1400 * (z.NS - 5000));
+    return col || z.E >= few || a.max_group_tiles > 16;
+  }
   const double steps =
       7.8 + 1.6e-6 * z.E +
       (rsddmm_rows_faster(z) ? rsddmm_rows_us(z) : rsddmm_slices_us(z)) +
@@ -1293,8 +1308,8 @@ Route rspmm_route(const DevAcsr& a, int dtype, int BH, int d) {
 Route fused_f32_route(const DevAcsr& a, int BH, int d) {
   return fused_rows_faster(Size(a, BH, d)) ? kRouteRows : kRouteSlices;
 }
-Route unfused_route(const DevAcsr& a, int dtype, int BH, int d) {
-  return chain_faster(a, dtype, BH, d) ? kRouteChain : kRouteSteps;
+Route unfused_route(const DevAcsr& a, int dtype, int BH, int d, bool col, bool values) {
+  return chain_faster(a, dtype, BH, d, col, values) ? kRouteChain : kRouteSteps;
 }
 
 namespace {

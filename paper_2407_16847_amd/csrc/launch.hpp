@@ -44,7 +44,8 @@ Route rsddmm_route(const DevAcsr& a, int dtype, int BH, int d);
 Route rspmm_route(const DevAcsr& a, int dtype, int BH, int d);   // both layouts
 Route fused_f32_route(const DevAcsr& a, int BH, int d);
 int fused_mfma_sets(const DevAcsr& a, int BH, int d);   // sets of wavefronts per tile group
-Route unfused_route(const DevAcsr& a, int dtype, int BH, int d);
+// values: the caller reads P afterwards
+Route unfused_route(const DevAcsr& a, int dtype, int BH, int d, bool colmajor, bool values);
 
 // Every launcher enqueues on `st` and returns the launch status.
 // dtype / out dtype: 0 = fp32, 1 = bf16.

@@ -67,11 +67,33 @@ def test_bf16_cases(d):
     assert _reached("sparse_mhsa_fwd", BF16, gpu.SETS, d, heads=[3]) == sets
 
 
+# launches away from the lines, with the faster side as measured (the time of
+# the other in brackets, us)
+MEASURED = [
+    # the chain in one kernel against its steps, bf16
+    ("sparse_mhsa_unfused", BF16, "window", {"w": 8}, 8192, 32, 128, "steps"),       # 137 (161)
+    ("sparse_mhsa_unfused", BF16, "window", {"w": 2}, 8192, 100, 64, "steps"),       # 238 (307)
+    ("sparse_mhsa_unfused", BF16, "window", {"w": 128}, 1024, 64, 64, "chain"),      # 45 (134)
+    ("sparse_mhsa_unfused", BF16, "window", {"w": 8}, 8192, 1, 128, "chain"),
+    ("sparse_mhsa_unfused", BF16, "window_global", {"w": 3, "n_global": 3}, 9000, 60, 64, "chain"),
+    ("sparse_mhsa_unfused, column-major", BF16, "window", {"w": 8}, 8192, 32, 128, "chain"),
+    ("sparse_mhsa_unfused_noalloc", BF16, "window", {"w": 4}, 12000, 57, 64, "chain"),   # 197 (209)
+    ("sparse_mhsa_unfused", BF16, "window", {"w": 4}, 12000, 57, 64, "steps"),       # 209 (256)
+    ("sparse_mhsa_unfused_noalloc", BF16, "dilated", {"w": 8, "dilation": 5}, 16288, 37, 128, "steps"),
+]
+
+
+@pytest.mark.parametrize("call,dtype,kind,params,L,heads,d,want", MEASURED)
+def test_the_faster_side_is_taken(call, dtype, kind, params, L, heads, d, want):
+    got, sets = splat.route(_acsr(kind, params, L), call, dtype, 1, heads, d)
+    assert (f"{got}:{sets}" if ":" in want else got) == want
+
+
 def test_argument_checks():
     a = _acsr("window", {"w": 5}, 65)
     lib, r = splat.load(), ctypes.c_int32(7)
     bad = [(None, 0, 0, 1, 1, 64, ctypes.byref(r)), (a.handle, 0, 0, 1, 1, 64, None),
-           (a.handle, 4, 0, 1, 1, 64, ctypes.byref(r)), (a.handle, -1, 0, 1, 1, 64, ctypes.byref(r)),
+           (a.handle, 6, 0, 1, 1, 64, ctypes.byref(r)), (a.handle, -1, 0, 1, 1, 64, ctypes.byref(r)),
            (a.handle, 0, 2, 1, 1, 64, ctypes.byref(r)), (a.handle, 0, 0, 0, 1, 64, ctypes.byref(r))]
     for args in bad:
         assert lib.splat_debug_route(*args, None) == 1          # INVALID_ARG
