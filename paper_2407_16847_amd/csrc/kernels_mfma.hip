@@ -439,10 +439,17 @@ __global__ __launch_bounds__(kThreads * NSET, D == 64 ? 4 : 2) void k_fused_mfma
 // heads 54 / 44; window 512 + 64 global, L = 4096, 16 heads 58 / 47 / 41, 32
 // heads 72 / 60 / 75, 64 heads 95 / 107; strided+local 128, L = 2048, 24 heads
 // (5 tiles) 11.3 / 12.5; full, L = 512, 8 heads 10.2 / 9.2 / 9.9.  Two sets
-// of d = 128 and four of d = 64 fill a CU's LDS and wavefronts.
+// of d = 128 and four of d = 64 fill a CU's LDS and wavefronts, so beyond a group
+// a CU two sets also cost each group its start and its end (20 ns at d = 128, 1
+// at 64): d = 128, window 3 + 27 global, L = 686, 104 heads 25 / 32 us, window 21
+// + 1 global, L = 1148, 82 heads 36 / 44, window 17 + 57 global, L = 4217, 75 heads
+// 110 / 135; d = 64, window 31 + 99 global, L = 633, 107 heads 18 / 21.
 int fused_mfma_sets(const DevAcsr& a, int BH, int d) {
+  constexpr int kCus = 256;
+  const double groups = (double)a.n_groups * BH;
   const double chain = (d == 64 ? 0.84 : 1.57) * a.max_group_tiles;
-  const double all = (d == 64 ? 2.5e-3 : 5.7e-3) * a.n_tiles * BH;
+  const double all = (d == 64 ? 2.5e-3 : 5.7e-3) * a.n_tiles * BH +
+                     (groups > kCus ? (d == 64 ? 1e-3 : 20e-3) * groups : 0);
   if (a.max_group_tiles < 8 || chain <= all) return 1;
   return d == 64 && a.max_group_tiles >= 16 && chain / 2 > all ? 4 : 2;
 }

@@ -80,6 +80,12 @@ MEASURED = [
     ("sparse_mhsa_unfused_noalloc", BF16, "window", {"w": 4}, 12000, 57, 64, "chain"),   # 197 (209)
     ("sparse_mhsa_unfused", BF16, "window", {"w": 4}, 12000, 57, 64, "steps"),       # 209 (256)
     ("sparse_mhsa_unfused_noalloc", BF16, "dilated", {"w": 8, "dilation": 5}, 16288, 37, 128, "steps"),
+    # sets of wavefronts in the fused bf16 forward
+    ("sparse_mhsa_fwd", BF16, "window_global", {"w": 3, "n_global": 27}, 686, 104, 128, "tiles:1"),
+    ("sparse_mhsa_fwd", BF16, "window_global", {"w": 17, "n_global": 57}, 4217, 75, 128, "tiles:1"),
+    ("sparse_mhsa_fwd", BF16, "window_global", {"w": 31, "n_global": 99}, 633, 107, 64, "tiles:1"),
+    ("sparse_mhsa_fwd", BF16, "full", {}, 777, 16, 128, "tiles:2"),
+    ("sparse_mhsa_fwd", BF16, "window_global", {"w": 512, "n_global": 64}, 4096, 16, 64, "tiles:4"),
 ]
 
 
