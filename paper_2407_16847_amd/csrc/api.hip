@@ -56,6 +56,10 @@ void plan_sizes(splat_acsr* h) {
     h->dev.max_group_tiles = std::max(h->dev.max_group_tiles, g.tile_end - g.tile_begin);
   h->dev.rows_aligned = a.nnz % 32 == 0;
   for (int32_t p : a.row_ptr) h->dev.rows_aligned = h->dev.rows_aligned && p % 32 == 0;
+  h->dev.columns = a.col_regular == 1;
+  h->dev.columns_step = false;
+  for (const splat::ColRun& c : a.cols)
+    h->dev.columns_step = h->dev.columns_step || (c.count > 1 && c.stride != 1);
   for (const splat::Group& g : a.groups)
     for (int w = 0; w < splat::kWavesPerGroup; ++w) {
       int32_t n = 0;

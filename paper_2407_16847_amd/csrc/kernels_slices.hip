@@ -1253,13 +1253,23 @@ bool rsddmm_bf16_slices(const DevAcsr& a, const Size& z) {
   return slc < tiles;
 }
 // R-SpMM window 512 + 64 global, L = 4096, 16 heads 130 / 80 us, 64 heads 267 /
-// 318; blocked 64, L = 1024, 16 heads 7.7 / 5.9; full, L = 1024, 64 heads 48 / 71.
+// 318; blocked 64, L = 1024, 16 heads 7.7 / 5.9; full, L = 1024, 64 heads 48 / 71;
+// L = 218, 113 heads 10.4 / 14.4; groups of one tile: dilated 13 / 6, L = 151, 25
+// heads 4.2 / 5.4, d = 128, dilated 24 / 6, L = 116, 30 heads 4.6 / 5.8.  One
+// choice for both layouts, whose results are the same bits.  Column-major values
+// cost the tile kernel more (dilated 40 / 3, L = 4106, 3 heads, d = 128 27 / 13), so
+// a handle that has them takes the slices further, but at d = 64 not for groups of
+// one tile (5.1 / 5.7), nor for columns that step beyond a chip's slices (dilated
+// 51 / 4, L = 947, 28 heads 14.1 / 19.1), whose places are looked up one by one.
 bool rspmm_bf16_slices(const DevAcsr& a, const Size& z) {
   const double k = (z.w + 1) / 2;
+  if (a.max_group_tiles <= 1 && !(a.columns && z.w == 2)) return false;
+  if (a.columns_step && z.w == 1 && z.NS > 768) return false;
+  const double group =
+      a.columns ? 4.5 + 2 * a.max_group_tiles : 2 + z.w / 2 + 2.2 * a.max_group_tiles;
   const double slc =
       2.5 + fmax(0.9 + 1.5 * k * z.chain, k * (4.5e-3 * z.NS + 1.1e-6 * z.C));
-  const double tiles =
-      2 + fmax(4.5 + 2 * a.max_group_tiles, 3.5e-3 * z.NS + 0.75e-6 * k * z.C);
+  const double tiles = 2 + fmax(group, 3.5e-3 * z.NS + 0.75e-6 * k * z.C);
   return slc < tiles;
 }
 

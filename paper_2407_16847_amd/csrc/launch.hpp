@@ -19,6 +19,8 @@ struct DevAcsr {
   int32_t n_tiles;
   int32_t max_group_tiles;  // tiles of the row group that has the most
   bool rows_aligned;        // every row's values begin on a 128-byte line of the head's
+  bool columns;             // the handle has the column-major layout
+  bool columns_step;        // ... and some column steps over rows
   const int32_t* row_ptr;   // L + 1
   const RowRuns* runs;      // L
   const int32_t* rows;      // L (grouped)

@@ -310,8 +310,8 @@ def test_chain_without_keys(gpu_lib):
 @pytest.mark.parametrize("heads", [2, 400])
 @pytest.mark.parametrize("kind,params,L", [c[:3] for c in CASES[:-1]])
 def test_steps_bf16(gpu_lib, kind, params, L, heads, d):
-    """Two heads take the slices, 400 the 128-row tile kernels (R-SDDMM at d = 64
-    the slices also for 400 heads of short or thin masks)."""
+    """Two heads take the slices but for the shortest masks, 400 the 128-row tile
+    kernels but for some short or thin ones."""
     splat = gpu_lib
     print(f"[gpu] steps bf16 {kind} {params} L={L} heads={heads} d={d}", flush=True)
     scale = 1.0 / math.sqrt(d)
