@@ -1242,9 +1242,14 @@ bool rspmm_rows_faster(const Size& z) { return rspmm_rows_us(z) < rspmm_slices_u
 // heads 14.7 / 6.9, 64 heads 18.6 / 20.7.  Past the caches (192 MB; twice that
 // where rows begin and end on lines) the slices' partial lines cost: window 128,
 // L = 4096, 64 heads 102 / 130, full, L = 1024, 64 heads 98 / 70, L = 2048, 32
-// heads 145 / 168.
+// heads 145 / 168.  Rows that begin and end on lines suit the tile kernel best
+// where its walk is short and the chip is full: full, L = 384, 402 heads 58 / 75,
+// L = 448, 382 heads 69 / 100, window 540, L = 352, 211 heads 29 / 36 (against: full, L =
+// 352, 304 heads 49 / 37; of 28 such launches 22 are faster over tiles by more than
+// 5%, 6 slower).
 bool rsddmm_bf16_slices(const DevAcsr& a, const Size& z) {
   const double k = (z.w + 1) / 2;
+  if (a.rows_aligned && a.max_group_tiles <= 11 && z.NS >= 1800) return false;
   const double value = z.E > (a.rows_aligned ? 96e6 : 48e6) ? 1.4e-6 : 0.75e-6;
   const double slc =
       2.5 + k * fmax(0.7 + 1.45 * z.chain, 5e-3 * z.NS + value * z.E);

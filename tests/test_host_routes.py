@@ -79,6 +79,10 @@ MEASURED = [
     ("sparse_mhsa_unfused_noalloc", BF16, "window", {"w": 4}, 12000, 57, 64, "chain"),   # 197 (209)
     ("sparse_mhsa_unfused", BF16, "window", {"w": 4}, 12000, 57, 64, "steps"),       # 209 (256)
     ("sparse_mhsa_unfused_noalloc", BF16, "dilated", {"w": 8, "dilation": 5}, 16288, 37, 128, "steps"),
+    # R-SDDMM, bf16, over slices or tiles
+    ("rsddmm", BF16, "full", {}, 384, 402, 64, "tiles"),                             # 58 (75)
+    ("rsddmm", BF16, "full", {}, 1024, 64, 64, "slices"),                            # 70 (98)
+    ("rsddmm", BF16, "window_global", {"w": 512, "n_global": 64}, 4096, 16, 64, "slices"),  # 91 (178)
     # R-SpMM, bf16, over slices or tiles; `columns` handles
     ("rspmm", BF16, "dilated", {"w": 51, "dilation": 4}, 947, 28, 64, "tiles"),      # 14.1 (19.1)
     ("rspmm", BF16, "dilated", {"w": 8, "dilation": 6}, 180, 2, 64, "tiles"),        # 5.1 (5.7)
