@@ -1292,7 +1292,12 @@ bool rspmm_bf16_slices(const DevAcsr& a, const Size& z) {
 // heads 236 / 254), and O alone costs less than O and P (values: P is stored;
 // d = 64, window 4, L = 12000, 57 heads 197 / 209; d = 128, dilated 8 / 5, L =
 // 16288, 37 heads 322 / 306): there only the thinnest masks.  fp32: strided+local
-// 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5.
+// 128, L = 2048, 12 heads 39.5 / 50.6; window 16, L = 256, one head 9.8 / 8.5; at d
+// = 128, where one workgroup's LDS fills a CU, window 1, L = 925, 19 heads 41 / 29,
+// full, L = 1523, 18 heads 426 / 336, dilated 12 / 5, L = 1968, 42 heads 144 / 117,
+// but a long group holds the steps up more (window 11 + 2 global, L = 1638, 48 heads
+// 194 / 257), and the column-major branch has its fourth launch (full, L = 968, 7
+// heads 84 / 123).
 bool chain_faster(const DevAcsr& a, int dtype, int BH, int d, bool col, bool values) {
   const Size z(a, BH, d);
   if (dtype != 0) {
@@ -1305,7 +1310,10 @@ bool chain_faster(const DevAcsr& a, int dtype, int BH, int d, bool col, bool val
       7.8 + 1.6e-6 * z.E +
       (rsddmm_rows_faster(z) ? rsddmm_rows_us(z) : rsddmm_slices_us(z)) +
       fmin(rspmm_rows_us(z), rspmm_slices_us(z));
-  return 3.2 + slices_us(z, 10, 4.2, (z.w + 1) / 2 * (1.2 + 5.6 * z.chain)) < steps;
+  const double walk = (z.w + 1) / 2 * (1.2 + 5.6 * z.chain);
+  const int64_t longest = (int64_t)a.max_group_tiles * a.n_groups;
+  const bool alone = d == 128 && !col && longest <= 2 * (int64_t)a.n_tiles;
+  return 3.2 + (alone ? slices_us(z, 15, 5.5, walk) : slices_us(z, 10, 4.2, walk)) < steps;
 }
 
 }  // namespace

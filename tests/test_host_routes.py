@@ -79,6 +79,11 @@ MEASURED = [
     ("sparse_mhsa_unfused_noalloc", BF16, "window", {"w": 4}, 12000, 57, 64, "chain"),   # 197 (209)
     ("sparse_mhsa_unfused", BF16, "window", {"w": 4}, 12000, 57, 64, "steps"),       # 209 (256)
     ("sparse_mhsa_unfused_noalloc", BF16, "dilated", {"w": 8, "dilation": 5}, 16288, 37, 128, "steps"),
+    # ... and fp32, d = 128
+    ("sparse_mhsa_unfused", F32, "window", {"w": 1}, 925, 19, 128, "steps"),         # 29 (41)
+    ("sparse_mhsa_unfused", F32, "full", {}, 1523, 18, 128, "steps"),                # 336 (426)
+    ("sparse_mhsa_unfused", F32, "window_global", {"w": 11, "n_global": 2}, 1638, 48, 128, "chain"),  # 194 (257)
+    ("sparse_mhsa_unfused, column-major", F32, "full", {}, 968, 7, 128, "chain"),    # 84 (123)
     # R-SDDMM, bf16, over slices or tiles
     ("rsddmm", BF16, "full", {}, 384, 402, 64, "tiles"),                             # 58 (75)
     ("rsddmm", BF16, "full", {}, 1024, 64, 64, "slices"),                            # 70 (98)
