@@ -336,11 +336,13 @@ __device__ __forceinline__ void mask_unit(float (&t)[16], uint32_t bits, int h) 
 }
 
 // The matrix cores multiply every key row by every query's weight, 0 for the
-// queries that do not have the key, and 0 * inf is NaN.  z turns NaN when V
-// holds an infinity or a NaN in half a unit in which some row lacks some key;
-// the slice's rows are then formed again row by row (the *_row functions
-// below).  With bf16 V no such check is made: there a row may see the keys of
-// its tile.
+// queries that do not have the key, and 0 * inf is NaN: with an infinity or a NaN
+// in V, rows that lack the key turn NaN as well.  z turns NaN when V holds one in
+// half a unit in which some row lacks some key; the lane's row is then marked by
+// a NaN, and combine forms such rows again one by one (in the chain all of the
+// slice's).  (combine would find them without z, but the fused loop without the
+// check is scheduled worse: window 256 + 32 global, L = 2048, 12 heads 59 -> 73 us.)
+// With bf16 V no such check is made: there a row may see the keys of its tile.
 template <typename T, int D>
 __device__ __forceinline__ void check_v(float& z, const typename Mat<T, D>::V& v, const Unit& u) {
   if constexpr (std::is_same<T, float>::value) {
@@ -362,7 +364,7 @@ struct Shared {
   float o[kWavesPerGroup][kWaveRows * OS];
   float m[kWavesPerGroup][kWaveRows];
   float l[kWavesPerGroup][kWaveRows];
-  unsigned redo;                                   // rows to be formed again row by row
+  int redo;                                        // the chain: some V value is not finite
 };
 
 template <typename OutT>
@@ -372,16 +374,14 @@ __device__ __forceinline__ void store_o4(OutT* p, f32x4_t v) {
 
 // Sum of the wavefronts' O^T, times inv(row i), written as whole rows: every
 // thread sums four features of one row at a time, eight lanes along a row.
-// CHECK: a row whose result is not finite is marked in sh.redo instead, for the
-// caller to form the marked rows again one by one.  That order of the sums may
-// stay within fp32's range where this one does not, and the row code keeps the
+// CHECK: a row whose result is not finite is not stored (O may lie over Q) but
+// formed by again(row): by its keys one after the other.  That order of the sums
+// may stay within fp32's range where this one does not, and the row code keeps the
 // fused kernel's weights at 1 and below, which reach 2^kRefSlack before the
-// division by their sum here.  (It would find what check_v finds too, but
-// without check_v the fused loop is scheduled worse: window 256 + 32 global, L =
-// 2048, 12 heads 59 -> 73 us.)
-template <int D, bool CHECK, typename OutT, typename F>
+// division by their sum here.  Each wavefront looks after the eight rows it sums.
+template <int D, bool CHECK, typename OutT, typename F, typename G>
 __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 32], const Slice& s,
-                                        OutT* Oh, F&& inv) {
+                                        OutT* Oh, F&& inv, G&& again) {
   constexpr int NB = D / 32, OS = Shared<D>::OS;
   float* const mine = sh.o[s.wave] + s.qi * OS;
 #pragma unroll
@@ -396,11 +396,10 @@ __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 3
   __syncthreads();
   const int r = threadIdx.x >> 3;                  // row of the slice
   const int lane_r = (int)__shfl(s.row_valid ? s.row : -1, r & 31, 64);
+  f32x4_t v[NB];
+  float z = 0.f;
   if (lane_r >= 0) {
     const float f = inv(r, lane_r);
-    OutT* const orow = Oh + (size_t)lane_r * D;
-    f32x4_t v[NB];
-    float z = 0.f;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int c = 4 * (threadIdx.x & 7) + 32 * k;
@@ -408,26 +407,20 @@ __device__ __forceinline__ void combine(Shared<D>& sh, const f32x16_t (&o)[D / 3
 #pragma unroll
       for (int w = 1; w < kWavesPerGroup; ++w) v[k] += *(const f32x4_t*)(sh.o[w] + r * OS + c);
       v[k] *= f;
+      if (CHECK)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) z = fmaf(v[k][e], 0.f, z);
+        for (int e = 0; e < 4; ++e) z = fmaf(v[k][e], 0.f, z);
     }
-    // nothing of such a row, or of one marked before, is stored: O may lie over Q
-    if (CHECK) {
-      if ((__ballot(z != z) >> (s.lane & 56)) & 0xffu) atomicOr(&sh.redo, 1u << r);
-      if ((sh.redo >> r) & 1u) return;
-    }
+  }
+  const uint64_t bad = CHECK ? __ballot(z != z) : 0;
+  if (lane_r >= 0 && ((bad >> (s.lane & 56)) & 0xffu) == 0) {
+    OutT* const orow = Oh + (size_t)lane_r * D;
 #pragma unroll
     for (int k = 0; k < NB; ++k) store_o4<OutT>(orow + 4 * (threadIdx.x & 7) + 32 * k, v[k]);
   }
-}
-
-// f(row) by the wavefronts in turn, for the rows of the slice set in `rows`
-template <typename F>
-__device__ __forceinline__ void for_rows(unsigned rows, const Slice& s, F&& f) {
-  for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
-    const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
-    if (i >= 0 && ((rows >> r) & 1u)) f(i);
-  }
+  if (CHECK && bad != 0)
+    for (int k = 0; k < 64; k += 8)
+      if ((bad >> k) & 0xffu) again(__builtin_amdgcn_readlane(lane_r, k));
 }
 
 // exp(x - m) as the row softmax forms it
@@ -587,7 +580,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     // the row's reference (log2 domain) and the sum of this half's keys
     float m = -INFINITY, l = 0.f;
     float z = 0.f;
-    if (threadIdx.x == 0) sh.redo = 0;
 
     float* const stage = sh.o[s.wave];
     Units it;
@@ -655,9 +647,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     }
 
     l += lane_xor32(l);
-    __syncthreads();
     if (s.h == 0) sh.m[s.wave][s.qi] = m, sh.l[s.wave][s.qi] = l;
-    if (z != z) sh.redo = ~0u;
     __syncthreads();
     // row i's reference over the wavefronts, and a wavefront's factor to it
     auto top = [&](int i) {
@@ -669,7 +659,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[b][r] *= f;
-    combine<D, std::is_same<T, float>::value, OutT>(sh, o, s, O + head, [&](int i, int row) {
+    if (z != z) o[0][0] = z;
+    auto inv = [&](int i, int row) {
       const float mt = top(i);
       float lt = 0.f;
 #pragma unroll
@@ -677,16 +668,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
       if (lt > 0.f) return 1.f / lt;
       // no key: 0; a NaN is in O already; keys that all score -inf: NaN
       return lt == 0.f && row_ptr[row] != row_ptr[row + 1] ? NAN : 0.f;
+    };
+    combine<D, std::is_same<T, float>::value, OutT>(sh, o, s, O + head, inv, [&](int i) {
+      if constexpr (std::is_same<T, float>::value)
+        fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
+                           O + head);
     });
     __syncthreads();   // LDS is reused by the next slice
-    if constexpr (std::is_same<T, float>::value)
-      if (sh.redo) {
-        for_rows(sh.redo, s, [&](int i) {
-          fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
-                             O + head);
-        });
-        __syncthreads();
-      }
   }
 }
 
@@ -936,7 +924,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
     float z = 0.f;
-    if (threadIdx.x == 0) sh.redo = 0;
     // the unit's values of this lane's row, 0 where the row lacks the key
     auto load_p = [&](float(&p)[16], const Unit& u) {
       const uint32_t bits = s.row_valid ? s.bits(u) : 0u;
@@ -987,19 +974,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
         for (int r = 0; r < 16; ++r) p[r] = pn[r];
       u = nu, more = next;
     }
-    if constexpr (kF32) {
-      __syncthreads();
-      if (z != z) sh.redo = ~0u;
-    }
-    combine<D, kF32, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
-    __syncthreads();   // LDS is reused by the next slice
-    if constexpr (kF32)
-      if (sh.redo) {
-        for_rows(sh.redo, s, [&](int i) {
-          spmm_row<D, OutT, COL>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+    if (z != z) o[0][0] = z;
+    combine<D, kF32, OutT>(
+        sh, o, s, O + head, [](int, int) { return 1.f; },
+        [&](int i) {
+          if constexpr (kF32)
+            spmm_row<D, OutT, COL>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
         });
-        __syncthreads();
-      }
+    __syncthreads();   // LDS is reused by the next slice
   }
 }
 
@@ -1155,19 +1137,24 @@ __global__ __launch_bounds__(kThreads, D == 64 && sizeof(T) == 2 ? 3 : 2) void k
       u = nu, nu = nnu, more = next, next = nnext;
     }
     if constexpr (kF32) {
+      // weights of 1 at most: only V can take a sum out of fp32's range
       __syncthreads();
-      if (z != z) sh.redo = ~0u;
-    }
-    combine<D, kF32, OutT>(sh, o, s, O + head, [](int, int) { return 1.f; });
-    __syncthreads();   // LDS is reused by the next slice
-    if constexpr (kF32)
+      if (z != z) sh.redo = 1;
+      __syncthreads();
       if (sh.redo) {   // from the P just written
         __threadfence_block();
-        for_rows(sh.redo, s, [&](int i) {
-          spmm_row<D, OutT, false>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
-        });
+        for (int r = s.wave; r < kWaveRows; r += kWavesPerGroup) {
+          const int i = __builtin_amdgcn_readlane(s.row_valid ? s.row : -1, r);
+          if (i >= 0)
+            spmm_row<D, OutT, false>(i, s.lane, runs, row_ptr, cols, L, nnz, Ph, V + head, O + head);
+        }
         __syncthreads();
+        continue;
       }
+    }
+    combine<D, false, OutT>(
+        sh, o, s, O + head, [](int, int) { return 1.f; }, [](int) {});
+    __syncthreads();   // LDS is reused by the next slice
   }
 }
 
