@@ -549,13 +549,14 @@ __global__ __launch_bounds__(kThreads) void k_fused_rows(
 // the global rows, 16 units per wavefront, is the longest chain.  Two
 // wavefronts per SIMD; three (168 registers, some spilled) took 86 us against
 // 63, and the next unit's products beside this one's softmax 65 against 60.
-template <typename T, int D, typename OutT>
+template <int D, typename OutT>
 __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     const Group* __restrict__ groups, const int32_t* __restrict__ rows,
     const int32_t* __restrict__ row_ptr, const RowRuns* __restrict__ runs,
     const Tile* __restrict__ tiles, const uint64_t* __restrict__ masks, int L, int n_slices,
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, float scale,
-    OutT* __restrict__ O) {
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    float scale, OutT* __restrict__ O) {
+  using T = float;
   using M = Mat<T, D>;
   constexpr int NB = D / 32;
   __shared__ __attribute__((aligned(16))) Shared<D> sh;
@@ -669,15 +670,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
       // no key: 0; a NaN is in O already; keys that all score -inf: NaN
       return lt == 0.f && row_ptr[row] != row_ptr[row + 1] ? NAN : 0.f;
     };
-    combine<D, std::is_same<T, float>::value, OutT>(sh, o, s, O + head, inv, [&](int i) {
-      if constexpr (std::is_same<T, float>::value)
-        fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale,
-                           O + head);
+    combine<D, true, OutT>(sh, o, s, O + head, inv, [&](int i) {
+      fused_row<D, OutT>(i, s.lane, runs, row_ptr, L, Q + head, K + head, V + head, scale, O + head);
     });
     __syncthreads();   // LDS is reused by the next slice
   }
 }
-
 
 // ------------------------------------------------------------ values in ACSR
 // Where the values of a row's keys of a unit sit: position `pos` of head bh
@@ -1338,20 +1336,20 @@ hipError_t fused_rows(const DevAcsr& a, int BH, const void* Q, const void* K, co
   return hipGetLastError();
 }
 
-template <typename T, int D>
+template <int D>
 hipError_t fused_d(const DevAcsr& a, int BH, const void* Q, const void* K, const void* V,
                    float scale, void* O, int out_dtype, hipStream_t st) {
   if (fused_f32_route(a, BH, D) == kRouteRows)
     return out_dtype == 0 ? fused_rows<D, float>(a, BH, Q, K, V, scale, O, st)
                           : fused_rows<D, __bf16>(a, BH, Q, K, V, scale, O, st);
   if (out_dtype == 0)
-    hipLaunchKernelGGL((k_fused_slices<T, D, float>), slice_grid(a, BH), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL((k_fused_slices<D, float>), slice_grid(a, BH), dim3(kThreads), 0, st,
                        a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, slices(a),
-                       (const T*)Q, (const T*)K, (const T*)V, scale, (float*)O);
+                       (const float*)Q, (const float*)K, (const float*)V, scale, (float*)O);
   else
-    hipLaunchKernelGGL((k_fused_slices<T, D, __bf16>), slice_grid(a, BH), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL((k_fused_slices<D, __bf16>), slice_grid(a, BH), dim3(kThreads), 0, st,
                        a.groups, a.rows, a.row_ptr, a.runs, a.tiles, a.masks, a.L, slices(a),
-                       (const T*)Q, (const T*)K, (const T*)V, scale, (__bf16*)O);
+                       (const float*)Q, (const float*)K, (const float*)V, scale, (__bf16*)O);
   return hipGetLastError();
 }
 
@@ -1445,8 +1443,8 @@ hipError_t bounds_probe(int kind, int index, int n, int* result) {
 
 hipError_t launch_fused_f32(const DevAcsr& a, int BH, int d, const void* Q, const void* K,
                             const void* V, float scale, void* O, int out_dtype, hipStream_t st) {
-  return d == 64 ? fused_d<float, 64>(a, BH, Q, K, V, scale, O, out_dtype, st)
-                 : fused_d<float, 128>(a, BH, Q, K, V, scale, O, out_dtype, st);
+  return d == 64 ? fused_d<64>(a, BH, Q, K, V, scale, O, out_dtype, st)
+                 : fused_d<128>(a, BH, Q, K, V, scale, O, out_dtype, st);
 }
 
 hipError_t launch_rsddmm(const DevAcsr& a, int dtype, int BH, int d, const void* Q, const void* K,
