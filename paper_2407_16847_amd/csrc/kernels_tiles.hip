@@ -257,17 +257,6 @@ __device__ __forceinline__ void store4_row(float* p, int idx, int n, const float
   }
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // Grid: x over blocks of rows, y over batch*head, so that the work-item
 // count of each dimension stays far below 2^32 at every allowed size.
 //

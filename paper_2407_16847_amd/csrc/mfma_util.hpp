@@ -1,6 +1,6 @@
 // mfma_util.hpp -- device helpers shared by the matrix-core kernels: operand
 // vector types, the bf16 32x32x16 MFMA, LDS transpose reads, global->LDS
-// loads, lane exchange and the ring barrier.
+// loads, lane exchange, reductions over a wavefront and the ring barrier.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,6 +41,18 @@ __device__ __forceinline__ float lane_xor32(float x) {
   const auto sw = __builtin_amdgcn_permlane32_swap(xi, xi, false, false);
   const int lane = __lane_id();
   return __builtin_bit_cast(float, lane < 32 ? sw[1] : sw[0]);
+}
+
+// over the 64 lanes
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
 // The same transpose read issued as inline assembly: the compiler then does
