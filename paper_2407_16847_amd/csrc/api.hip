@@ -286,7 +286,8 @@ bool meet(const void* a, size_t na, const void* b, size_t nb) {
 }
 
 // The unfused chain.  keep_values: the caller reads P in S (and Pt) afterwards;
-// without it a bf16 chain that runs as one kernel leaves them alone.
+// without it a chain that runs as one kernel leaves them alone, but for P of
+// fp32 inputs, from which it redoes slices whose V is not finite.
 splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
                          const void* Q, const void* K, const void* V, float scale, float* S,
                          float* Pt, void* O, splat_dtype out_dtype, float alpha,
@@ -316,7 +317,7 @@ splat_status run_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H
     const bool values = keep_values || dtype != SPLAT_BF16;
     if (used_colmajor) *used_colmajor = col ? 1 : 0;
     return launched(splat::launch_chain(h->dev, dtype, B * H, d, Q, K, V, scale,
-                                        values ? S : nullptr, values && col ? Pt : nullptr, O,
+                                        values ? S : nullptr, keep_values && col ? Pt : nullptr, O,
                                         out_dtype, st),
                     "sparse_mhsa_unfused");
   }
