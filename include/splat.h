@@ -357,7 +357,9 @@ splat_status splat_rspmm_colmajor(splat_acsr_t h, splat_dtype dtype, int32_t B, 
  * branch.  *used_colmajor (if non-NULL) is set to 1 on the column-major
  * branch, 0 otherwise.  Results as the individual calls' (within their
  * rounding: one kernel may form P and O without storing S first; S then holds
- * P, and Pt its column-major copy, as after the individual calls).
+ * P, and Pt its column-major copy, as after the individual calls).  O may take
+ * the place of Q or K, and on the column-major branch lie inside S, whose values
+ * it then replaces: such calls run as the single steps.
  */
 #define SPLAT_DENSE_ALPHA 0.10f
 splat_status splat_sparse_mhsa_unfused(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H,
@@ -398,9 +400,10 @@ splat_status splat_sparse_mhsa_unfused_noalloc(splat_acsr_t h, splat_dtype dtype
  * with an online (running max / running sum) softmax over the planned key
  * tiles, so S and P never reach device memory.  Q, K, V: [B,H,L,d] of `dtype`;
  * O: [B,H,L,d] of `out_dtype`.  bf16 inputs: scores and softmax in fp32, P
- * rounded toward zero to bf16 for the P V product (the row sum adds the same
+ * rounded to nearest even bf16 for the P V product (the row sum adds the same
  * rounded values), fp32 accumulation.  fp32 inputs: fp32 throughout.  A row
- * without non-zeros gets O = 0.
+ * without non-zeros gets O = 0; with fp32 inputs a row whose scores are all -inf
+ * gets NaN.
  */
 splat_status splat_sparse_mhsa_fwd(splat_acsr_t h, splat_dtype dtype, int32_t B, int32_t H, int32_t d,
                                    const void* Q, const void* K, const void* V, float scale,

@@ -528,7 +528,8 @@ __global__ __launch_bounds__(kThreads) void k_fused_rows(
 // its units, the four (reference, sum, O) combined at the end.  A row takes its
 // first unit's maximum as its reference and keeps it while later maxima stay
 // within 2^kRefSlack of it: p then lies in [0, 2^kRefSlack], in fp32 as exact
-// as below 1, and few units rescale O.
+// as below 1, and few units rescale O.  (Rows whose O leaves fp32's range for it
+// are formed again, see combine.)
 //
 // fp32 is bound by the matrix cores: a unit is 64 (d = 64) v_mfma_f32_32x32x2
 // of 64 cycles.  Full mask, L = 2048, 64 heads, d = 64: 651 us, 106 TFLOP/s of
@@ -578,8 +579,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fused_slices(
     bool more = it.next(u);
     if (more) fetch_k<T, D>(stage, Kh, s, u, L);
     while (more) {
-      // d = 128: V is loaded where no K is held, half a unit at a time, which
-      // keeps the kernel in 256 registers (two wavefronts per SIMD)
+      // d = 128: V is loaded where no K is held, half a unit at a time, for two
+      // wavefronts per SIMD (256 registers, and 22 spilled: 92 bytes a lane)
       wait_loads();
       typename M::Row k;
       load_k<T, D>(k, stage, s);
@@ -985,10 +986,13 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void k_rspmm_slices(
 // heads, 1.1 GB of P: 569 us against 1006 for three launches that store S, read
 // it, store P and read it), by the dependent loads of one slice at small ones
 // (blocked 64, L = 1024, 16 heads: 7.1 us with O alone, 9.9 with P, 26.5 for
-// three launches).  Window 128, L = 1024, 64 heads: 45 us with P, 57 with Pt as
-// well (134 for four launches).  Registers: three wavefronts per SIMD at bf16,
-// d = 64 (two: 53 us against 45 with P, window 128), two elsewhere (three: 159
-// us against 101, dilated 2, L = 4096, d = 128).
+// three launches).  Window 128, L = 1024, 64 heads, while the buffers fit the
+// caches: 45 us with P, 57 with Pt as well (134 for four launches); over new inputs
+// from call to call 80 with Pt.  Registers: three wavefronts per SIMD at bf16, d =
+// 64 (two: 53 us against 45 with P, window 128), with 2 registers spilled with P,
+// 10 with Pt; two at bf16, d = 128 (three: 159 us against 101, dilated 2, L = 4096)
+// and at fp32, d = 64.  At fp32, d = 128 the values wait apart from K, 87 KB of LDS
+// in all: one workgroup a CU, one wavefront per SIMD.
 template <typename T, int D, typename OutT, int OUT>
 __global__ __launch_bounds__(kThreads, D == 64 && sizeof(T) == 2 ? 3 : 2) void k_chain_slices(
     const Group* __restrict__ groups, const int32_t* __restrict__ rows,
